@@ -3,7 +3,8 @@ public entry points of paper_2603_13618_amd.
 
 Each listed case stands for a use:
 
-* `shear128_f32`      a small D2Q9 grid (the double shear layer's 128^2) run many steps per call
+* `shear128_f32`      a whole short run on a small D2Q9 grid, the double shear layer's 128^2: the
+                      initial state and 100 steps in one call
 * `step256_f32`       one step per call on a small grid: a loop that looks at the flags after each step
 * `ragged_f32`        a D2Q9 grid whose sides are odd
 * `smooth4096_f32`    the headline D2Q9 grid, FP32, row-interleaved state
@@ -12,7 +13,8 @@ Each listed case stands for a use:
 * `riemann2048_bgk`   D2Q25 finite volume, single distribution, four-quadrant Riemann problem
 * `riemann1024_ddf`   D2Q25 double distribution (f, g), the grid of the paper's 2D Riemann runs
 * `ragged_ddf_f64`    the double distribution in FP64 on a grid that is no multiple of a tile
-* `sod1024_ddf`       the paper's shock tube: a pseudo-1D grid, two rows, many steps per call
+* `sod1024_ddf`       the paper's shock tube, a pseudo-1D grid of two rows: the initial state and
+                      64 steps in one call
 * `adjoint1024_f32`   gradient of the summed KL sensor, forward and backward with checkpoints
 * `cycle1024_f32`     one regridding cycle: steps, moments, macroscopic sensors, buffer layer, tile
                       counts, clustering on the host
@@ -227,7 +229,7 @@ def prepare(case, seed):
         return dict(case=case, rho=rho, ux=ux.requires_grad_(True), uy=uy.requires_grad_(True))
     lat = lks.Lattice(**kw)
     lat.init(*fields)
-    return dict(case=case, lat=lat)
+    return dict(case=case, lat=lat, fields=fields)
 
 
 # --------------------------------------------------------------------------
@@ -242,6 +244,8 @@ def run(state):
         gux, guy = torch.autograd.grad(loss, (state["ux"], state["uy"]))
         return dict(loss=loss.detach(), gux=gux, guy=guy)
     lat = state["lat"]
+    if case["kind"] == "sod" or case.get("field") == "shear":
+        lat.init(*state["fields"])              # a whole short run, from its initial fields
     lat.step(case["steps"])
     out = dict(state=lat.state, sensors=lat.sensors, flags=lat.flags, sums=lat.sums)
     if case["kind"] == "cycle":
