@@ -690,13 +690,17 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(Q25Wave
     if (far) {
         kl = R(0);
         first = true;
+        // cells within the longer series (most of them) take that alone
+        const bool series = xmax <= KlCut<R>::v;
         d2q25_deq<R>(drho, rho, ux, uy, tm1, [&](int ia, int ib, R deq) {
             const R d = vin[5 * ia + ib];
             const R feq = R(gh5_w(ia) * gh5_w(ib)) * rho0 + deq;
             const R x = (d - deq) * rcp(feq);
             xmin = first ? x : fmin(xmin, x);
             first = false;
-            kl += feq * kl_phi(x);
+            R phi = x * x * kl_series(x);
+            if (!series) phi = fabs(x) <= KlCut<R>::v ? phi : kl_general(x);
+            kl += feq * phi;
         });
     }
 
@@ -961,23 +965,29 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
     });
     const bool nonpos = !(eqmin > R(0)) || !(Tc > R(0)) || !(xlo > R(-1));
     if (!(xmax <= KlShortCut<R>::v) && !nonpos) {
-        // rare: some population far from equilibrium (or NaN): the closed
-        // form, one population at a time.  Cells with a positivity fault
-        // skip it: their S_KL is +inf whatever the sums (on the paper's
+        // rare: some population far from equilibrium (or NaN): the longer
+        // series or the general form.  Cells with a positivity fault skip
+        // it: their S_KL is +inf whatever the sums (on the paper's
         // supersonic Riemann problem No. 3 that is half of the cells)
         klf = R(0);
         klg = R(0);
-        sfor25<25>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            const R w = R(gh5_w(i / 5) * gh5_w(i % 5));
-            const R deq = deqv[i];
-            const R feq = w * rho0 + deq;
-            const R dgeq = gfac * (Tc * deq + tm1 * (w * rho0));
-            const R geq = gfac * (w * rho0) + dgeq;
-            klf += feq * kl_phi((fc[i] - deq) * rcp(feq));
-            klg += geq * kl_phi((gc[i] - dgeq) * rcp(geq));
-            __builtin_amdgcn_sched_barrier(0);
-        });
+        // one population at a time (a scheduling barrier each); cells within
+        // the longer series (most of them) take that alone
+        auto closed = [&](auto&& phi) {
+            sfor25<25>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                const R w = R(gh5_w(i / 5) * gh5_w(i % 5));
+                const R deq = deqv[i];
+                const R feq = w * rho0 + deq;
+                const R dgeq = gfac * (Tc * deq + tm1 * (w * rho0));
+                const R geq = gfac * (w * rho0) + dgeq;
+                klf += feq * phi((fc[i] - deq) * rcp(feq));
+                klg += geq * phi((gc[i] - dgeq) * rcp(geq));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        if (xmax <= KlCut<R>::v) closed([](R x) { return x * x * kl_series(x); });
+        else closed([](R x) { return kl_phi(x); });
     }
     // the total energy flux q = sum v (g^neq + |v|^2/2 f^neq) (S_Q), and the
     // heat fluxes relative to u: with sum f^neq = 0 and sum v f^neq = 0,

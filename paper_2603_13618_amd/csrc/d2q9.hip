@@ -144,18 +144,29 @@ __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau
                 if (cy9(i) != 0) pyy += fneq;
                 if (cx9(i) * cy9(i) != 0) pxy += R(cx9(i) * cy9(i)) * fneq;
             }
-            // Rare: some population far from equilibrium (or NaN).  There the
-            // smallest x is needed too (x > -1 is f > 0); on the short-series
-            // branch |x| <= 0.03 already implies it.
+            // Rare: some population far from equilibrium (or NaN).  Beyond the
+            // longer series the smallest x is needed too (x > -1 is f > 0);
+            // |x| <= 0.1 already implies it.
+            // Cells within the longer series (most of them) take that alone.
             far = !(xmax <= KlShortCut<R>::v);
             if (far) {
                 kl = R(0);
+                const bool series = xmax <= KlCut<R>::v;
+                if (series) {
 #pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    const R feq = w9<R>(i) * rho0 + deq[i];
-                    const R x = (d[i] - deq[i]) * rcp(feq);
-                    xmin = i == 0 ? x : fmin(xmin, x);
-                    kl += feq * kl_phi(x);
+                    for (int i = 0; i < 9; ++i) {
+                        const R feq = w9<R>(i) * rho0 + deq[i];
+                        const R x = (d[i] - deq[i]) * rcp(feq);
+                        kl += feq * (x * x * kl_series(x));
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) {
+                        const R feq = w9<R>(i) * rho0 + deq[i];
+                        const R x = (d[i] - deq[i]) * rcp(feq);
+                        xmin = i == 0 ? x : fmin(xmin, x);
+                        kl += feq * kl_phi(x);
+                    }
                 }
             }
         }
