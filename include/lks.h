@@ -206,7 +206,13 @@ typedef struct {
                              1 plain, 2 non-temporal (a launch hint only:
                              results are identical).  D2Q9 every storage
                              type; D2Q25 FP32 on grids of whole tiles      */
-    int32_t launch_steps; /* fused D2Q9 steps per launch: 0 or 1 one, 2 two
+    int32_t launch_steps; /* fused D2Q9 steps per launch: 0 picks (several steps
+                             of a tile per launch where a call has them, with
+                             automatic launch_rows, launch_vec and launch_nt;
+                             the state changes buffer as often as with one,
+                             and the call's last step is a launch of its own,
+                             so the other buffer holds the state before it),
+                             1 one, 2 two
                              (temporal blocking: the state crosses HBM once
                              per two steps; D2Q9 without extension sensors;
                              an odd last step of a reduction batch runs
@@ -216,8 +222,8 @@ typedef struct {
                              A launch hint: state, sensors, flags and the
                              fault count are the same bits and the per-step
                              FP64 sums agree to FP64 rounding (each cell's
-                             terms are widened to FP64 before any add), but
-                             the state changes buffer once per launch, so
+                             terms are widened to FP64 before any add); with
+                             2 the state changes buffer once per launch, so
                              lks_current names the buffer that holds it      */
 } lks_config;
 
@@ -229,13 +235,15 @@ typedef struct {
                              F64): base planes, then the extension planes     */
     uint8_t* flags;       /* [ny][nx]                                          */
     double* sums;         /* [max_steps][LKS_NSUMS]                            */
-    void* scratch;        /* >= lks_scratch_bytes(cfg) bytes, 256-B aligned    */
+    void* scratch;        /* lks_scratch_bytes(cfg) bytes, 256-B aligned       */
     size_t scratch_bytes;
 } lks_buffers;
 
-/* Device bytes of scratch the configuration needs (per-block FP64 partial
- * sums and counters; with LKS_MODEL_DDF also 6 values per cell that the
- * step's f kernel hands to its g kernel).  0 for an invalid configuration. */
+/* Device bytes of scratch for the configuration (per-block FP64 partial
+ * sums and counters; lks_create also takes a smaller buffer that holds the
+ * partial sums of the one-step kernels, and then runs those; with
+ * LKS_MODEL_DDF also 6 values per cell that the step's f kernel hands to its g
+ * kernel).  0 for an invalid configuration. */
 size_t lks_scratch_bytes(const lks_config* cfg);
 
 /* Number of base sensor planes of a lattice with the BGK model (3 for D2Q9,

@@ -604,6 +604,442 @@ __global__ __launch_bounds__(kBlock) LKS_CELL_KERNEL_ATTR void d2q9_fused_lds(
     block_sums(acc, partials + (long long)blockIdx.x * kNsums);
 }
 
+// k steps of one tile per launch, small grids.  A step of a small grid is
+// launch, load and store latency, not arithmetic: a workgroup that loads its
+// TX x TY tile with a ring of k cells advances the tile k steps (odd k <= K,
+// the ring shrinking by one cell a step) for one launch.  Step 0 gathers its
+// populations from global memory, the later ones from LDS, where a step's
+// post-collision values, rounded to the storage type as a stored state would
+// be, replace those of the step before the last; one cell per thread and
+// iteration, one copy of the cell update for all steps, so that little code is
+// fetched.  Every cell's arithmetic is cell_update: state, sensors, flags and
+// fault counts are the same bits as k one-step launches, and since each step's
+// sums are taken over the same tiles in the same order whatever k is, so are
+// the sums of any split of a run into launches.
+// FP32, us per step of a 64-step call (the one-step row kernel in brackets):
+// 64^2 1.8 (14.8), 128^2 1.9 (16.4), 256^2 2.6 (16.1); FP64 128^2 3.4 (14.9),
+// BF16 256^2 2.5 (7.1).
+template <typename S, int TX, int TY, int K> struct TileSteps {
+    using raw = typename Store<S>::raw;
+    using R = typename Store<S>::real;
+    static constexpr int kCells = (TX + 2 * (K - 1)) * (TY + 2 * (K - 1));   // cells step 0 may produce
+    static constexpr int kThreads = kCells >= 1024 ? 1024 : (kCells + kWave - 1) / kWave * kWave;
+    static constexpr int kTile = TX * TY;
+    static constexpr int kSums = 6;                                          // sums a D2Q9 step has
+    static_assert(kTile % kWave == 0, "a wave reads whole rows of terms");
+};
+
+// Whether the tiles of T cells with a ring of K along an axis of n cells reach
+// at most one period beyond it on either side (what the kernels wrap).
+constexpr bool tile_fits(int n, int T, int K) { return n >= K && (n - 1) / T * T + T + K <= 2 * n; }
+
+// Sum of one value per lane over the wave, in lane 63: additions of the lanes
+// below within rows of 16 (DPP row shifts), then of the rows.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+    return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum_lane63(double v)
+{
+    v = dpp_add<0x111, 0xf>(v);      // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);      // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);      // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);      // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+template <typename S, int TX, int TY, int K>
+__global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile_kernel(
+    D2Q9Args a, int k, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
+    typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
+    int first, unsigned long long* __restrict__ faults)
+{
+    using G = TileSteps<S, TX, TY, K>;
+    using R = typename G::R;
+    using raw = typename G::raw;
+    __shared__ raw buf[2][9 * G::kCells];
+    __shared__ R terms[2][G::kSums][G::kTile];
+
+    const int nx = a.nx, ny = a.ny;
+    const int tiles_x = (nx + TX - 1) / TX;
+    const int X0 = (blockIdx.x % tiles_x) * TX, Y0 = (blockIdx.x / tiles_x) * TY;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nwaves = blockDim.x / kWave;
+    const unsigned pp = (unsigned)a.L.pp, pr = (unsigned)a.L.pr, plane = (unsigned)a.plane;
+
+    constexpr bool F32 = sizeof(R) == 4;
+    const R rho0 = F32 ? R(a.rho0_f) : R(a.rho0);
+    const R inv_tau = F32 ? R(a.inv_tau_f) : R(1.0 / a.tau);
+    R th[3][2];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        th[s][0] = F32 ? R(a.thr_f[s][0]) : R(a.thr[s][0]);
+        th[s][1] = F32 ? R(a.thr_f[s][1]) : R(a.thr[s][1]);
+    }
+    const int h0 = k - 1, W0 = TX + 2 * h0;        // LDS cell (x, y) of the tile: (y + h0) W0 + x + h0
+    unsigned nfault = 0;
+
+    // the sums of one step from its terms: one wave per quantity (the sums
+    // of steps before `first` are not kept)
+    auto reduce = [&](int j) {
+        if (j < first) return;
+        for (int q = wave; q < G::kSums; q += nwaves) {
+            double v = 0.0;
+#pragma unroll
+            for (int m = 0; m < G::kTile / kWave; ++m) v += (double)terms[j & 1][q][m * kWave + lane];
+            v = wave_sum_lane63(v);
+            // quantities 0..2: mass, momentum; 3..5: the sensors, sums 4..6
+            double* out = partials + ((long long)(j - first) * gridDim.x + blockIdx.x) * kNsums;
+            if (lane == kWave - 1) {
+                out[q < 3 ? q : q + 1] = v;
+                if (q == 0) out[3] = out[7] = 0.0;
+            }
+        }
+    };
+
+    for (int j = 0; j < k; ++j) {
+        const int h = k - 1 - j, W = TX + 2 * h, n = W * (TY + 2 * h);
+        const float rW = 1.0f / (float)W;
+        const bool last = j == k - 1;
+        for (int e = threadIdx.x; e < n; e += blockDim.x) {
+            // e = r W + c; exact: e < 4096 and (e + 0.5)/W is at least 1/(2W) off an integer
+            const int r = (int)(((float)e + 0.5f) * rW);
+            const int x = e - r * W - h, y = r - h;
+            const int cell = (y + h0) * W0 + x + h0;
+            R d[9];
+            if (j == 0) {
+                const int gx = X0 + x, gy = Y0 + y;
+                // one period off at most (tile_fits)
+                unsigned xs[3], ys[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    int u = gx + q - 1, v = gy + q - 1;
+                    u += u < 0 ? nx : 0;
+                    u -= u >= nx ? nx : 0;
+                    v += v < 0 ? ny : 0;
+                    v -= v >= ny ? ny : 0;
+                    xs[q] = (unsigned)u;
+                    ys[q] = (unsigned)v * pr;
+                }
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    d[i] = Store<S>::to_real(fin[i * pp + ys[1 - cy9(i)] + xs[1 - cx9(i)]]);
+            } else {
+                const raw* src = buf[(j - 1) & 1];
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    d[i] = Store<S>::to_real(src[i * G::kCells + cell - cy9(i) * W0 - cx9(i)]);
+            }
+            R drho, jx, jy;
+            const CellSense<R> cs = cell_update<R, true, true>(d, rho0, inv_tau, drho, jx, jy);
+            if (!last) {
+                raw* dst = buf[j & 1];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) dst[i * G::kCells + cell] = Store<S>::from_real(d[i]);
+            }
+            if (x >= 0 && x < TX && y >= 0 && y < TY) {
+                const bool own = X0 + x < nx && Y0 + y < ny;
+                const int t = y * TX + x;
+                terms[j & 1][0][t] = own ? drho : R(0);
+                terms[j & 1][1][t] = own ? jx : R(0);
+                terms[j & 1][2][t] = own ? jy : R(0);
+                terms[j & 1][3][t] = own ? cs.kl : R(0);
+                terms[j & 1][4][t] = own ? cs.neq : R(0);
+                terms[j & 1][5][t] = own ? cs.pi : R(0);
+                nfault += own && cs.fault ? 1u : 0u;
+                if (last && own) {
+                    const unsigned off = (unsigned)(Y0 + y) * (unsigned)nx + (unsigned)(X0 + x);
+                    const unsigned po = (unsigned)(Y0 + y) * pr + (unsigned)(X0 + x);
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) fout[i * pp + po] = Store<S>::from_real(d[i]);
+                    LevelAcc lv;
+                    const R sv[3] = {cs.kl, cs.neq, cs.pi};
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                    sens[off] = cs.kl;
+                    sens[plane + off] = cs.neq;
+                    sens[2 * plane + off] = cs.pi;
+                    flags[off] = cs.fault ? uint8_t(0x82) : uint8_t(lv.level());
+                }
+            }
+        }
+        __syncthreads();
+        // the terms of step j are rewritten in step j + 2, behind another barrier
+        reduce(j);
+    }
+    if (nfault) atomicAdd(faults, (unsigned long long)nfault);
+}
+
+// Three steps of one tile per launch, mid-size and large grids.  A one-step
+// kernel moves 85 B per cell and step (FP32) and waits for HBM; three steps
+// for one pass leave the VALU issue as the bound.  A workgroup of NW waves owns
+// 64 columns and 2 NW rows, two rows a wave, one lane a column.  Step 0 reads
+// its populations from global memory (the tile and a ring of two cells, whose
+// cells are dealt out densely over the waves) and writes the post-collision
+// values, rounded to the storage type, to LDS; step 1 (the tile and a ring of
+// one cell) reads them, holds its results in registers across a barrier and
+// writes them in their place; step 2 stores the state, sensors and flags.  In
+// place, the 68 x 20 cells take 49 KB in FP32, so that several workgroups share
+// a CU and one's loads and stores hide behind another's arithmetic.  K = 1: a
+// single step on the same tiles, so that every step's sums are added in the
+// same order whichever launch it runs in.  Cell arithmetic: cell_update.
+// Eight waves: 57 wave updates for the 48 that the tile itself needs; six waves
+// (64 x 12 tiles) and sixteen (64 x 32, one workgroup a CU) measured 204 and 179
+// against 142 us per step at FP32 4096^2.
+// us per step (the one-step row kernel in brackets): FP32 512^2 4.0 (17.5),
+// 1024^2 10.7 (17.9), 2048^2 36.5 (68.8), 4096^2 142 (239); FP64 1024^2 25.3
+// (33.6), 4096^2 356 (468); BF16 1024^2 10.9 (16.1), 4096^2 140 (178).
+template <typename S, int K, int NW> struct BandSteps {
+    using raw = typename Store<S>::raw;
+    using R = typename Store<S>::real;
+    static_assert(K == 1 || K == 3, "one or three steps");
+    static constexpr int TX = kWave, TY = 2 * NW, H0 = K - 1, W0 = TX + 2 * H0;
+    static constexpr int kCells = K == 1 ? 1 : W0 * (TY + 2 * H0);
+};
+
+// Sums over the wave of six values: halves, then 16-lane rows, of two values
+// are exchanged and added (each lane then carries one of them), then the rows
+// are added up.  Lane 0, 16, 32, 48 of `a`: values 0, 2, 1, 3; lane 0, 32 of
+// `b`: values 4, 5.
+__device__ __forceinline__ double swap_add32(double x, double y)
+{
+    const unsigned long long ux = __builtin_bit_cast(unsigned long long, x), uy = __builtin_bit_cast(unsigned long long, y);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ux, (unsigned)uy, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ux >> 32), (unsigned)(uy >> 32), false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double x, double y)
+{
+    const unsigned long long ux = __builtin_bit_cast(unsigned long long, x), uy = __builtin_bit_cast(unsigned long long, y);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ux, (unsigned)uy, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ux >> 32), (unsigned)(uy >> 32), false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double row_sum(double v)
+{
+    v = dpp_add<0x128, 0xf>(v);      // row_ror:8
+    v = dpp_add<0x124, 0xf>(v);      // row_ror:4
+    v = dpp_add<0x122, 0xf>(v);      // row_ror:2
+    return dpp_add<0x121, 0xf>(v);   // row_ror:1
+}
+__device__ __forceinline__ void wave_sums6(const double (&v)[6], double& a, double& b)
+{
+    const double p = swap_add32(v[0], v[1]), q = swap_add32(v[2], v[3]), r = swap_add32(v[4], v[5]);
+    a = row_sum(swap_add16(p, q));
+    b = row_sum(swap_add16(r, r));
+}
+
+template <typename S, int K, int NW, bool NT>
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 ? 4 : 2))) void d2q9_band_kernel(
+    D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
+    typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
+    int first, int nblocks, unsigned long long* __restrict__ faults)
+{
+    using G = BandSteps<S, K, NW>;
+    using R = typename G::R;
+    using raw = typename G::raw;
+    constexpr int TX = G::TX, TY = G::TY, H0 = G::H0, W0 = G::W0, C = G::kCells;
+    __shared__ raw buf[9 * C];
+    __shared__ double red[K][NW][6];
+
+    // the XCD that runs a workgroup is its id mod 8: each takes runs of eight
+    // tiles along x
+    const int tile = blockIdx.x / 64 * 64 + blockIdx.x % 8 * 8 + blockIdx.x / 8 % 8;
+    if (tile >= nblocks) return;                    // whole workgroups
+    const int nx = a.nx, ny = a.ny;
+    const int tiles_x = (nx + TX - 1) / TX;
+    const int X0 = (tile % tiles_x) * TX, Y0 = (tile / tiles_x) * TY;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+
+    constexpr bool F32 = sizeof(R) == 4;
+    const R rho0 = F32 ? R(a.rho0_f) : R(a.rho0);
+    const R inv_tau = F32 ? R(a.inv_tau_f) : R(1.0 / a.tau);
+    R th[3][2];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        th[s][0] = F32 ? R(a.thr_f[s][0]) : R(a.thr[s][0]);
+        th[s][1] = F32 ? R(a.thr_f[s][1]) : R(a.thr[s][1]);
+    }
+    unsigned nfault = 0;
+    // one period off at most (tile_fits)
+    auto wrap = [](int j, int n) {
+        j += j < 0 ? n : 0;
+        return j - (j >= n ? n : 0);
+    };
+    unsigned xs[3];                                 // this lane's column and its neighbours
+#pragma unroll
+    for (int q = 0; q < 3; ++q) xs[q] = (unsigned)wrap(X0 + lane + q - 1, nx);
+
+    // ring cell e of the ring of H cells: top and bottom rows, then the sides
+    auto ring_cell = [&](auto hc, int e, int& x, int& y) {
+        constexpr int H = decltype(hc)::value, W = TX + 2 * H;
+        if (e < 2 * H * W) {
+            const int r = e / W;
+            x = e - r * W - H;
+            y = r < H ? r - H : TY + r - H;
+        } else {
+            const int s = e - 2 * H * W, c = s % (2 * H);
+            x = c < H ? c - H : TX + c - H;
+            y = s / (2 * H);
+        }
+    };
+    auto put = [&](int cell, const R (&d)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) buf[i * C + cell] = Store<S>::from_real(d[i]);
+    };
+    auto get = [&](int cell, R (&d)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) d[i] = Store<S>::to_real(buf[i * C + cell - cy9(i) * W0 - cx9(i)]);
+    };
+    // the two owned rows of this wave at one step, after their gather
+    auto owned = [&](int j, R (&d)[2][9], bool last) {
+        double v[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) v[q] = 0.0;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int y = 2 * wave + r;
+            const bool own = X0 + lane < nx && Y0 + y < ny;
+            R drho, jx, jy;
+            const CellSense<R> cs = cell_update<R, true, true>(d[r], rho0, inv_tau, drho, jx, jy);
+            // each cell's terms widen to FP64 before any add
+            v[0] += (double)(own ? drho : R(0));
+            v[1] += (double)(own ? jx : R(0));
+            v[2] += (double)(own ? jy : R(0));
+            v[3] += (double)(own ? cs.kl : R(0));
+            v[4] += (double)(own ? cs.neq : R(0));
+            v[5] += (double)(own ? cs.pi : R(0));
+            nfault += own && cs.fault ? 1u : 0u;
+            if (last && own) {
+                LevelAcc lv;
+                const R sv[3] = {cs.kl, cs.neq, cs.pi};
+#pragma unroll
+                for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                const unsigned X = (unsigned)(X0 + lane);
+                const long long prow = a.L.at(0, Y0 + y, 0), srow = (long long)(Y0 + y) * nx;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const R o[1] = {d[r][i]};
+                    store_vec<S, 1, NT>(fout + (prow + i * a.L.pp) + X, o);
+                }
+                const R kl[1] = {cs.kl}, neq[1] = {cs.neq}, pi[1] = {cs.pi};
+                const uint8_t fl[1] = {cs.fault ? uint8_t(0x82) : uint8_t(lv.level())};
+                store_pack<R, 1, NT>(sens + srow + X, kl);
+                store_pack<R, 1, NT>(sens + (a.plane + srow) + X, neq);
+                store_pack<R, 1, NT>(sens + (2 * a.plane + srow) + X, pi);
+                store_pack<uint8_t, 1, NT>(flags + srow + X, fl);
+            }
+        }
+        double sa, sb;
+        wave_sums6(v, sa, sb);
+        if (lane % 16 == 0) {
+            const int row = lane / 16;              // rows 0 .. 3 of sa: values 0, 2, 1, 3
+            red[j][wave][row == 1 ? 2 : row == 2 ? 1 : row] = sa;
+            if (row % 2 == 0) red[j][wave][4 + row / 2] = sb;
+        }
+    };
+    auto ring_update = [&](R (&d)[9]) {
+        R drho, jx, jy;
+        (void)cell_update<R, true, true>(d, rho0, inv_tau, drho, jx, jy);
+    };
+
+    {   // ---- step 0: from global memory
+        R d[2][9];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            static_for<9>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                const int ys = wrap(Y0 + 2 * wave + r - cy9(i), ny);
+                d[r][i] = Store<S>::to_real((fin + a.L.at(i, ys, 0))[xs[1 - cx9(i)]]);
+            });
+        }
+        R g[9];
+        int cell = 0;
+        bool ring = false;
+        if constexpr (K > 1) {
+            constexpr int n = (TX + 2 * H0) * (TY + 2 * H0) - TX * TY;
+            static_assert(n <= NW * kWave, "one ring cell a thread");
+            int x, y;
+            ring = (int)threadIdx.x < n;
+            if (ring) {
+                ring_cell(std::integral_constant<int, H0>{}, threadIdx.x, x, y);
+                cell = (y + H0) * W0 + x + H0;
+                long long row[3];
+                int col[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    row[q] = (long long)wrap(Y0 + y + q - 1, ny) * a.L.pr;
+                    col[q] = wrap(X0 + x + q - 1, nx);
+                }
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    g[i] = Store<S>::to_real(fin[i * a.L.pp + row[1 - cy9(i)] + col[1 - cx9(i)]]);
+            }
+        }
+        owned(0, d, K == 1);
+        if constexpr (K > 1) {
+            put((2 * wave + H0) * W0 + lane + H0, d[0]);
+            put((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            if (ring) {
+                ring_update(g);
+                put(cell, g);
+            }
+        }
+    }
+    __syncthreads();
+    if constexpr (K > 1) {
+        {   // ---- step 1: in place
+            R d[2][9], g[9];
+            int cell = 0;
+            constexpr int n = (TX + 2) * (TY + 2) - TX * TY;
+            // the ring goes to the waves that had none, or less, of step 0's
+            const int e = NW * kWave - 1 - (int)threadIdx.x;
+            const bool ring = e < n;
+            get((2 * wave + H0) * W0 + lane + H0, d[0]);
+            get((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            owned(1, d, false);
+            if (ring) {
+                int x, y;
+                ring_cell(std::integral_constant<int, 1>{}, e, x, y);
+                cell = (y + H0) * W0 + x + H0;
+                get(cell, g);
+                ring_update(g);
+            }
+            __syncthreads();
+            put((2 * wave + H0) * W0 + lane + H0, d[0]);
+            put((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            if (ring) put(cell, g);
+        }
+        __syncthreads();
+        {   // ---- step 2: to global memory
+            R d[2][9];
+            get((2 * wave + H0) * W0 + lane + H0, d[0]);
+            get((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            owned(2, d, true);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x < K * kNsums) {
+        const int j = threadIdx.x / kNsums, k = threadIdx.x % kNsums;
+        double s = 0.0;
+        if (k != 3 && k != 7) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += red[j][w][k < 3 ? k : k - 1];
+        }
+        if (j >= first) partials[((long long)(j - first) * nblocks + tile) * kNsums + k] = s;
+    }
+    if (nfault) atomicAdd(faults, (unsigned long long)nfault);
+}
+
 // Two fused steps per pass over HBM (temporal blocking): the API keeps
 // only the last step's sensors and flags, so a wave can advance its cells two
 // steps from one read of the state.  Each wave owns a strip of kSweepW = 60
@@ -826,6 +1262,131 @@ hipError_t launch_d2q9_two(int dtype, const D2Q9Args& a, const void* fin, void* 
     case 1: return launch_two<float>(a, fin, fout, sens, flags, part_a, part_b, faults, s);
     case 2: return launch_two<bf16_t>(a, fin, fout, sens, flags, part_a, part_b, faults, s);
     case 3: return launch_two<f16_t>(a, fin, fout, sens, flags, part_a, part_b, faults, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <typename S, int TX, int TY, int K>
+static hipError_t launch_tile_steps(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
+                                    uint8_t* flags, double* partials, int first, unsigned long long* faults,
+                                    hipStream_t st)
+{
+    using G = TileSteps<S, TX, TY, K>;
+    if (k < 1 || k > K || !tile_fits(a.nx, TX, K) || !tile_fits(a.ny, TY, K)) return hipErrorInvalidValue;
+    const int cells = (TX + 2 * (k - 1)) * (TY + 2 * (k - 1));
+    const int threads = cells >= G::kThreads ? G::kThreads : (cells + kWave - 1) / kWave * kWave;
+    const unsigned blocks = (unsigned)(((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY));
+    d2q9_tile_kernel<S, TX, TY, K><<<dim3(blocks), dim3(threads), 0, st>>>(
+        a, k, (const typename G::raw*)fin, (typename G::raw*)fout, (typename G::R*)sens, flags, partials, first,
+        faults);
+    return hipGetLastError();
+}
+
+constexpr int kBandWaves = 8;
+constexpr int kBandX = kWave, kBandY = 2 * kBandWaves, kBandK = 3;
+
+template <typename S>
+static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
+                                    uint8_t* flags, double* partials, int first, unsigned long long* faults,
+                                    hipStream_t st)
+{
+    using raw = typename Store<S>::raw;
+    using R = typename Store<S>::real;
+    constexpr int NW = kBandWaves;
+    constexpr bool kHalf = sizeof(raw) == 2;
+    if ((k != 1 && k != 3) || !tile_fits(a.nx, kBandX, kBandK) || !tile_fits(a.ny, kBandY, kBandK))
+        return hipErrorInvalidValue;
+    const int n = ((a.nx + kBandX - 1) / kBandX) * ((a.ny + kBandY - 1) / kBandY);
+    const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(NW * kWave);
+    const raw* in = (const raw*)fin;
+    raw* out = (raw*)fout;
+    R* sv = (R*)sens;
+    if (k == 3 && a.nt_stores)
+        d2q9_band_kernel<S, 3, NW, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+    else if (k == 3)
+        d2q9_band_kernel<S, 3, NW, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+    else if (kHalf && a.nt_stores)
+        d2q9_band_kernel<S, 1, NW, kHalf><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+    else
+        d2q9_band_kernel<S, 1, NW, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+    return hipGetLastError();
+}
+
+// Tile forms (F(form, columns, rows, most steps)): the tile kernel's three,
+// then the band kernel.
+#define LKS_TILE_FORMS(F) F(1, 8, 8, 7) F(2, 16, 16, 7) F(3, 32, 16, 5)
+constexpr int kBandForm = 4;
+
+// The smallest tiles that one workgroup a CU can take (the fewest cells for
+// the ring's share of work: at FP32 128^2 8 x 8 tiles 1.9, 16 x 16 2.2 us a step;
+// at 256^2 16 x 16 2.6, 32 x 16 2.9, band 3.7; at 320^2 32 x 16 3.2, band 3.9; with
+// more tiles than CUs 16 x 16 takes 4.4 there), then the band kernel (384^2: 4.0
+// against 5.6), and on grids too narrow for it the largest tile that fits.
+// 32 x 16 tiles of FP64 cells do not fit the LDS.
+int d2q9_tile_of(int dtype, int nx, int ny)
+{
+    constexpr long long kCUs = 256;
+#define LKS_TILE_FITS(V, TX, TY, K)                                                                         \
+    if ((V < 3 || dtype != 0) && tile_fits(nx, TX, K) && tile_fits(ny, TY, K) &&                            \
+        (long long)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) <= kCUs)                                     \
+        return V;
+    LKS_TILE_FORMS(LKS_TILE_FITS)
+#undef LKS_TILE_FITS
+    if (tile_fits(nx, kBandX, kBandK) && tile_fits(ny, kBandY, kBandK)) return kBandForm;
+    if (dtype != 0 && tile_fits(nx, 32, 5) && tile_fits(ny, 16, 5)) return 3;
+    if (tile_fits(nx, 16, 7) && tile_fits(ny, 16, 7)) return 2;
+    return tile_fits(nx, 8, 7) && tile_fits(ny, 8, 7) ? 1 : 0;
+}
+
+int d2q9_tile_steps(int tile)
+{
+    switch (tile) {
+#define LKS_TILE_STEPS(V, TX, TY, K) case V: return K;
+    LKS_TILE_FORMS(LKS_TILE_STEPS)
+#undef LKS_TILE_STEPS
+    case kBandForm: return kBandK;
+    default: return 0;
+    }
+}
+
+int d2q9_tile_blocks(int tile, int nx, int ny)
+{
+    switch (tile) {
+#define LKS_TILE_BLOCKS(V, TX, TY, K) case V: return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
+    LKS_TILE_FORMS(LKS_TILE_BLOCKS)
+#undef LKS_TILE_BLOCKS
+    case kBandForm: return ((nx + kBandX - 1) / kBandX) * ((ny + kBandY - 1) / kBandY);
+    default: return 0;
+    }
+}
+
+bool d2q9_tile_single(int dtype, int tile, bool nt) { return tile != kBandForm || dtype > 1 || !nt; }
+
+template <typename S>
+static hipError_t launch_tile_form(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
+                                   uint8_t* flags, double* partials, int first, unsigned long long* faults,
+                                   hipStream_t st)
+{
+    switch (a.tile) {
+    case 1: return launch_tile_steps<S, 8, 8, 7>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+    case 2: return launch_tile_steps<S, 16, 16, 7>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+    case 3:
+        if constexpr (sizeof(typename Store<S>::raw) <= 4)
+            return launch_tile_steps<S, 32, 16, 5>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+        return hipErrorInvalidValue;
+    case kBandForm: return launch_band_steps<S>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
+                            uint8_t* flags, double* partials, int first, unsigned long long* faults, hipStream_t s)
+{
+    switch (dtype) {
+    case 0: return launch_tile_form<double>(a, k, fin, fout, sens, flags, partials, first, faults, s);
+    case 1: return launch_tile_form<float>(a, k, fin, fout, sens, flags, partials, first, faults, s);
+    case 2: return launch_tile_form<bf16_t>(a, k, fin, fout, sens, flags, partials, first, faults, s);
+    case 3: return launch_tile_form<f16_t>(a, k, fin, fout, sens, flags, partials, first, faults, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -189,6 +189,15 @@ lks::D2Q25Args d2q25_args(const lks_config& c)
     return a;
 }
 
+// The tile form of a configuration's fused steps (0 = none): automatic launch
+// shapes only, without extension sensors.
+int tile_of(const lks_config& c)
+{
+    if (c.lattice != LKS_D2Q9 || c.ext_mask || c.launch_steps || c.launch_rows || c.launch_vec || c.launch_nt)
+        return 0;
+    return lks::d2q9_tile_of(c.dtype, c.nx, c.ny);
+}
+
 // workgroups of one step's cell kernel: the most any vector width that
 // lks_create may pick uses (the automatic sweep length grows with the tile
 // count, so the narrowest vector does not always have the most workgroups)
@@ -204,9 +213,9 @@ int step_blocks(const lks_config& c)
 }
 
 // steps whose partial sums share the scratch before one reduction launch
-int chunk_steps(const lks_config& c)
+int chunk_steps(const lks_config& c, int blocks)
 {
-    const long long per_step = (long long)step_blocks(c) * lks::kNsumsHost * sizeof(double);
+    const long long per_step = (long long)blocks * lks::kNsumsHost * sizeof(double);
     long long k = (16LL << 20) / (per_step > 0 ? per_step : 1);
     if (k < 1) k = 1;
     if (k > kMaxChunk) k = kMaxChunk;
@@ -214,10 +223,32 @@ int chunk_steps(const lks_config& c)
     return (int)k;
 }
 
+size_t partials_for(const lks_config& c, int blocks)
+{
+    const size_t b = (size_t)chunk_steps(c, blocks) * (size_t)blocks * lks::kNsumsHost * sizeof(double);
+    return (b + 255) / 256 * 256;
+}
+
+// steps of one tile launch whose sums a call can keep
+int tile_kept(const lks_config& c, int tile)
+{
+    const int k = lks::d2q9_tile_steps(tile);
+    return k < c.max_steps ? k : c.max_steps;
+}
+
+// bytes of partial sums without and with the tile form's workgroups: the
+// first is the least lks_create takes (a scratch buffer of that size runs the
+// row kernels where the tile form's partials do not fit), the second what
+// lks_scratch_bytes asks for (room for the steps of one tile launch at least)
+size_t least_partials(const lks_config& c) { return partials_for(c, step_blocks(c)); }
 size_t partials_bytes(const lks_config& c)
 {
-    const size_t b = (size_t)chunk_steps(c) * (size_t)step_blocks(c) * lks::kNsumsHost * sizeof(double);
-    return (b + 255) / 256 * 256;
+    const int tile = tile_of(c), nt = lks::d2q9_tile_blocks(tile, c.nx, c.ny);
+    const size_t least = least_partials(c);
+    if (!tile) return least;
+    const size_t one = ((size_t)tile_kept(c, tile) * nt * lks::kNsumsHost * sizeof(double) + 255) / 256 * 256;
+    const size_t p = partials_for(c, nt) > one ? partials_for(c, nt) : one;
+    return p > least ? p : least;
 }
 
 // the double distribution's per-cell hand-over between its two kernels
@@ -257,6 +288,9 @@ struct lks_ctx {
     lks::D2Q25Args a25;
     int nblocks;
     int nblocks2;          // workgroups of the two-step launches (launch_steps 2), else 0
+    int nblocks_t;         // workgroups of the tile launches (a9.tile), else 0
+    int slots_t;           // steps whose tile partial sums fit (1 .. kMaxChunk)
+    bool single_t;         // single steps run in the tile form too
     double* partials;
     unsigned long long* faults;
     char err[kErrLen];     // fixed storage: reporting an error allocates nothing
@@ -364,6 +398,13 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     c->a25.nt_stores = a.nt_stores;
     c->nblocks = cfg.lattice == LKS_D2Q25 ? c->a25.nblocks : a.g.nblocks;
     c->nblocks2 = cfg.launch_steps == 2 ? lks::d2q9_two_blocks(cfg.dtype, cfg.nx, cfg.ny) : 0;
+    // the tile form where the partial sums that one launch may keep fit
+    a.tile = tile_of(cfg);
+    c->nblocks_t = lks::d2q9_tile_blocks(a.tile, cfg.nx, cfg.ny);
+    const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
+    c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
+    if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
+    c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0);
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -376,6 +417,61 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     // alone (in the one-step kernel)
     if (cfg.launch_steps == 2 && k > 1) k &= ~1LL;
     c->chunk = (int)(k < 1 ? 1 : k);
+}
+
+// Sums of the reference parts of a step: mass, and energy on D2Q25 (sum_i w_i
+// |v_i|^2 / 2 = 1; the double distribution adds (C_v - 1) rho0 of g per cell).
+lks_status finalize(lks_ctx* c, int nblocks, int nsteps, int64_t row0)
+{
+    const double mass_ref = (double)c->n * c->cfg.rho0;
+    const double energy_ref = c->cfg.lattice != LKS_D2Q25 ? 0.0 : (ddf(c->cfg) ? cv_of(c->cfg) * mass_ref : mass_ref);
+    return hip_check(c, lks::launch_finalize(c->partials, nblocks, nsteps, c->buf.sums, row0, c->cfg.max_steps,
+                                             mass_ref, energy_ref, c->stream), "finalize kernel");
+}
+
+// Steps of the next launch when `left` >= 1 steps of a call remain in the tile
+// form.  An odd number, so that the state changes buffer as often as with one
+// step per launch, and the call's last step alone: the other buffer then holds
+// the state before it, as with one step per launch.  As even a split over the
+// fewest launches as that allows; where single steps run in the row kernel
+// (band form), threes and at most three single steps at the end.
+int tile_part(const lks_ctx* c, int left)
+{
+    const int most = lks::d2q9_tile_steps(c->a9.tile), m = left - 1;
+    if (m == 0) return 1;
+    if (!c->single_t) return m >= most ? most : 1;
+    int q = (m + most - 1) / most;
+    if ((q ^ m) & 1) ++q;
+    const int p = m / q;
+    return p % 2 ? p : (p + 1 <= most && m - (p + 1) >= q - 1 ? p + 1 : p - 1);
+}
+
+// A batch of tile launches: as many of the call's `left` remaining steps as
+// one reduction launch can take, no single step that the row kernel does
+// better.  The sums of steps that a later step of the call overwrites are not
+// kept.  *taken = steps run (0: the next step belongs to the row kernel).
+lks_status tile_batch(lks_ctx* c, int left, int* taken)
+{
+    int m = 0, kept = 0;
+    while (m < left) {
+        const int p = tile_part(c, left - m);
+        // of the launch's p steps, those among the call's last max_steps
+        const int behind = left - m - c->cfg.max_steps;
+        const int first = behind <= 0 ? 0 : (behind < p ? behind : p);
+        if ((p == 1 && !c->single_t) || kept + p - first > c->slots_t) break;
+        hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, c->a9, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
+                                             c->buf.sensors, c->buf.flags,
+                                             c->partials + (size_t)kept * c->nblocks_t * lks::kNsumsHost, first,
+                                             c->faults, c->stream);
+        if (lks_status st = hip_check(c, e, "step kernel")) return st;
+        c->cur = 1 - c->cur;
+        kept += p - first;
+        m += p;
+    }
+    *taken = m;
+    if (lks_status st = finalize(c, c->nblocks_t, kept, c->steps + m - kept)) return st;
+    c->steps += m;
+    return LKS_OK;
 }
 
 // The step loop of lks_step and lks_step_noalloc (c valid).
@@ -391,7 +487,15 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
     const lks::D2Q9Args& a = c->a9;
     int done = 0;
     while (done < nsteps) {
-        int m = (nsteps - done) < c->chunk ? (nsteps - done) : c->chunk;
+        int singles = nsteps - done;            // steps for the one-step (or two-step) kernels
+        if (fused && !q25 && a.tile) {
+            int taken = 0;
+            if (lks_status st = tile_batch(c, nsteps - done, &taken)) return st;
+            done += taken;
+            if (taken) continue;
+            singles = nsteps - done;            // the last few, in the row kernel
+        }
+        int m = singles < c->chunk ? singles : c->chunk;
         // two steps per launch: the batch takes whole pairs; a step without a
         // partner (the odd end of a call, or batches of one) is a batch of
         // its own in the one-step kernel
@@ -431,13 +535,7 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
             }
             if (lks_status st = hip_check(c, e, "step kernel")) return st;
         }
-        const double mass_ref = (double)c->n * c->cfg.rho0;
-        // sum_i w_i |v_i|^2 / 2 = 1 on D2Q25; the double distribution adds
-        // (C_v - 1) rho0 of g per cell
-        const double energy_ref = !q25 ? 0.0 : (ddf(c->cfg) ? cv_of(c->cfg) * mass_ref : mass_ref);
-        hipError_t e = lks::launch_finalize(c->partials, nb, m, c->buf.sums, c->steps,
-                                            c->cfg.max_steps, mass_ref, energy_ref, c->stream);
-        if (lks_status st = hip_check(c, e, "finalize kernel")) return st;
+        if (lks_status st = finalize(c, nb, m, c->steps)) return st;
         c->steps += m;
         done += m;
     }
@@ -507,13 +605,15 @@ lks_status lks_create(const lks_config* cfg, const lks_buffers* buf, void* hip_s
     if (!out) return fail(nullptr, LKS_EINVAL, "out is NULL");
     *out = nullptr;
     if (lks_status st = check_create(cfg, buf, true)) return st;
-    const size_t need = scratch_for(*cfg);
+    // a buffer of the least size is accepted, and the tile form used if its partials fit
+    const size_t least = kHeader + least_partials(*cfg) + aux_bytes(*cfg);
+    const size_t partials = buf->scratch_bytes >= scratch_for(*cfg) ? partials_bytes(*cfg) : least_partials(*cfg);
+    const size_t need = least;
     if (buf->scratch_bytes < need) return fail(nullptr, LKS_EINVAL, "scratch too small: need %zu bytes", need);
     if (!aligned(buf->scratch, 8)) return fail(nullptr, LKS_EINVAL, "scratch must be 8-byte aligned");
     lks_ctx* c = new (std::nothrow) lks_ctx();
     if (!c) return fail(nullptr, LKS_EINVAL, "out of host memory");
-    setup_ctx(c, *cfg, *buf, static_cast<hipStream_t>(hip_stream), static_cast<char*>(buf->scratch),
-              partials_bytes(*cfg));
+    setup_ctx(c, *cfg, *buf, static_cast<hipStream_t>(hip_stream), static_cast<char*>(buf->scratch), partials);
     *out = c;
     return LKS_OK;
 }
@@ -731,6 +831,9 @@ lks_status lks_step_from(lks_ctx* c, const void* src, void* dst)
     hipError_t e = c->cfg.lattice == LKS_D2Q25
                        ? lks::launch_d2q25(c->cfg.dtype, c->a25, src, dst, c->buf.sensors,
                                            c->buf.flags, c->partials, c->faults, c->stream)
+                   : c->single_t
+                       ? lks::launch_d2q9_tile(c->cfg.dtype, c->a9, 1, src, dst, c->buf.sensors, c->buf.flags,
+                                               c->partials, 0, c->faults, c->stream)
                        : lks::launch_d2q9(c->cfg.dtype, lks::kFused, c->a9, src, dst,
                                           c->buf.sensors, c->buf.flags, c->partials, c->faults,
                                           c->stream);

@@ -63,6 +63,7 @@ struct D2Q9Args {
     float thr_f[4][2];
     ExtArgs x;
     int nt_stores;            // fused step: non-temporal stores (large states)
+    int tile;                 // tile form of the fused steps (d2q9_tile_of), 0 = none
 };
 
 struct D2Q25Args {
@@ -104,6 +105,23 @@ hipError_t launch_d2q9_two(int dtype, const D2Q9Args& a, const void* fin, void* 
                            hipStream_t s);
 // workgroups of one launch_d2q9_two launch
 int d2q9_two_blocks(int dtype, int nx, int ny);
+
+// k fused D2Q9 steps of each tile per launch (odd k <= steps of the tile form
+// a.tile); the partial sums of step j >= first go to partials + (j - first) *
+// blocks * kNsums, those of earlier steps nowhere
+hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
+                            uint8_t* flags, double* partials, int first, unsigned long long* faults,
+                            hipStream_t s);
+// The tile form for a grid (0 = none), the most steps a launch of it takes and
+// its workgroups.
+int d2q9_tile_of(int dtype, int nx, int ny);
+int d2q9_tile_steps(int tile);
+int d2q9_tile_blocks(int tile, int nx, int ny);
+// Whether single steps run in the tile form too: not on FP32 and FP64 states
+// beyond the last-level cache, where the row kernel's 16-byte accesses pay
+// (one step at 4096^2: FP32 246 against 253 us, FP64 473 against 495; BF16 184
+// against 176, FP32 2048^2 75 against 74).
+bool d2q9_tile_single(int dtype, int tile, bool nt);
 
 hipError_t launch_d2q25(int dtype, const D2Q25Args& a, const void* fin, void* fout, void* sens,
                         uint8_t* flags, double* partials, unsigned long long* faults,
