@@ -404,7 +404,8 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
-    c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0);
+    c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0,
+                                                  cfg.layout == LKS_LAYOUT_ROWS, vec == wide_vec(cfg.dtype));
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;

@@ -117,11 +117,13 @@ hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin
 int d2q9_tile_of(int dtype, int nx, int ny);
 int d2q9_tile_steps(int tile);
 int d2q9_tile_blocks(int tile, int nx, int ny);
-// Whether single steps run in the tile form too: not on FP32 and FP64 states
-// beyond the last-level cache, where the row kernel's 16-byte accesses pay
-// (one step at 4096^2: FP32 246 against 253 us, FP64 473 against 495; BF16 184
-// against 176, FP32 2048^2 75 against 74).
-bool d2q9_tile_single(int dtype, int tile, bool nt);
+// Whether single steps run in the tile form too: not on FP32 and FP64
+// row-interleaved states beyond the last-level cache (nt) whose rows the row
+// kernel takes with its widest accesses.  One step, row kernel / tile form:
+// FP32 4096^2 246 / 253 us, 8192^2 952 / 1019, FP64 4096^2 499 / 508; but BF16
+// 184 / 176, FP32 plane-major 4096^2 287 / 263, odd rows (one cell per thread)
+// FP32 4001 x 3000 260 / 236, FP64 757 / 420.
+bool d2q9_tile_single(int dtype, int tile, bool nt, bool rows, bool wide);
 
 hipError_t launch_d2q25(int dtype, const D2Q25Args& a, const void* fin, void* fout, void* sens,
                         uint8_t* flags, double* partials, unsigned long long* faults,
