@@ -754,11 +754,13 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(Q25Wave
                 if (a.mask & (1u << (kExtFlagShift + q))) lv.add(xv[q], R(a.x.thr[q][0]), R(a.x.thr[q][1]));
             }
         }
-        sens[off] = s_kl;
-        sens[plane + off] = neq;
-        sens[2 * plane + off] = s_pi;
-        sens[3 * plane + off] = s_q;
-        flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
+        if (!a.quiet) {
+            sens[off] = s_kl;
+            sens[plane + off] = neq;
+            sens[2 * plane + off] = s_pi;
+            sens[3 * plane + off] = s_q;
+            flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
+        }
         if (fault) atomicAdd(faults, 1ull);
         acc[0] = (double)drho;
         acc[1] = (double)jx;
@@ -1161,9 +1163,11 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
                 if (a.mask & (1u << (kExtFlagShift + q))) lv.add(xv[q], R(a.x.thr[q][0]), R(a.x.thr[q][1]));
             });
         }
+        if (!a.quiet) {
 #pragma unroll
-        for (int s = 0; s < 5; ++s) sens[s * plane + off] = sv[s];
-        flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
+            for (int s = 0; s < 5; ++s) sens[s * plane + off] = sv[s];
+            flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
+        }
         if (fault) atomicAdd(faults, 1ull);
         acc[0] = (double)drho;
         acc[1] = (double)jx;
@@ -1283,13 +1287,14 @@ static hipError_t launch_ddf_tile(const D2Q25Args& a, const void* fin, void* fou
     const bool whole = a.nx % TX == 0 && a.ny % TY == 0;
     constexpr bool kNT = std::is_same<S, float>::value && TX * sizeof(R) >= 128;
     const bool nt = kNT && whole && a.nt_stores;
-    if (a.x.mask && nt)
+    const bool ext = a.x.mask && !a.quiet;
+    if (ext && nt)
         d2q25_ddf_kernel<S, TX, TY, true, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
-    else if (a.x.mask && whole)
+    else if (ext && whole)
         d2q25_ddf_kernel<S, TX, TY, true, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
-    else if (a.x.mask)
+    else if (ext)
         d2q25_ddf_kernel<S, TX, TY, true, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (nt)
@@ -1332,13 +1337,14 @@ static hipError_t launch_tile(const D2Q25Args& a, const void* fin, void* fout, v
     const bool whole = a.nx % TX == 0 && a.ny % TY == 0;
     constexpr bool kNT = std::is_same<S, float>::value && TX * sizeof(R) >= 128;
     const bool nt = kNT && whole && a.nt_stores;
-    if (a.x.mask && nt)
+    const bool ext = a.x.mask && !a.quiet;
+    if (ext && nt)
         d2q25_kernel<S, TX, TY, true, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
-    else if (a.x.mask && whole)
+    else if (ext && whole)
         d2q25_kernel<S, TX, TY, true, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
-    else if (a.x.mask)
+    else if (ext)
         d2q25_kernel<S, TX, TY, true, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (nt)

@@ -758,14 +758,18 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
                     const unsigned po = (unsigned)(Y0 + y) * pr + (unsigned)(X0 + x);
 #pragma unroll
                     for (int i = 0; i < 9; ++i) fout[i * pp + po] = Store<S>::from_real(d[i]);
-                    LevelAcc lv;
-                    const R sv[3] = {cs.kl, cs.neq, cs.pi};
+                    // a call's last step is a launch of its own: longer
+                    // launches' sensors and flags would be overwritten
+                    if (k == 1) {
+                        LevelAcc lv;
+                        const R sv[3] = {cs.kl, cs.neq, cs.pi};
 #pragma unroll
-                    for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
-                    sens[off] = cs.kl;
-                    sens[plane + off] = cs.neq;
-                    sens[2 * plane + off] = cs.pi;
-                    flags[off] = cs.fault ? uint8_t(0x82) : uint8_t(lv.level());
+                        for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                        sens[off] = cs.kl;
+                        sens[plane + off] = cs.neq;
+                        sens[2 * plane + off] = cs.pi;
+                        flags[off] = cs.fault ? uint8_t(0x82) : uint8_t(lv.level());
+                    }
                 }
             }
         }
@@ -784,8 +788,7 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
 // cells are dealt out densely over the waves) and writes the post-collision
 // values, rounded to the storage type, to LDS; step 1 (the tile and a ring of
 // one cell) reads them, holds its results in registers across a barrier and
-// writes them in their place; step 2 stores the state, sensors and flags.  In
-// place, the 68 x 20 cells take 49 KB in FP32, so that several workgroups share
+// writes them in their place; step 2 stores the state.  In place, the 68 x 20 cells take 49 KB in FP32, so that several workgroups share
 // a CU and one's loads and stores hide behind another's arithmetic.  K = 1: a
 // single step on the same tiles, so that every step's sums are added in the
 // same order whichever launch it runs in.  Cell arithmetic: cell_update.
@@ -920,10 +923,6 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
             v[5] += (double)(own ? cs.pi : R(0));
             nfault += own && cs.fault ? 1u : 0u;
             if (last && own) {
-                LevelAcc lv;
-                const R sv[3] = {cs.kl, cs.neq, cs.pi};
-#pragma unroll
-                for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
                 const unsigned X = (unsigned)(X0 + lane);
                 const long long prow = a.L.at(0, Y0 + y, 0), srow = (long long)(Y0 + y) * nx;
 #pragma unroll
@@ -931,12 +930,20 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
                     const R o[1] = {d[r][i]};
                     store_vec<S, 1, NT>(fout + (prow + i * a.L.pp) + X, o);
                 }
-                const R kl[1] = {cs.kl}, neq[1] = {cs.neq}, pi[1] = {cs.pi};
-                const uint8_t fl[1] = {cs.fault ? uint8_t(0x82) : uint8_t(lv.level())};
-                store_pack<R, 1, NT>(sens + srow + X, kl);
-                store_pack<R, 1, NT>(sens + (a.plane + srow) + X, neq);
-                store_pack<R, 1, NT>(sens + (2 * a.plane + srow) + X, pi);
-                store_pack<uint8_t, 1, NT>(flags + srow + X, fl);
+                // a call's last step is a launch of its own: longer launches'
+                // sensors and flags would be overwritten
+                if constexpr (K == 1) {
+                    LevelAcc lv;
+                    const R sv[3] = {cs.kl, cs.neq, cs.pi};
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                    const R kl[1] = {cs.kl}, neq[1] = {cs.neq}, pi[1] = {cs.pi};
+                    const uint8_t fl[1] = {cs.fault ? uint8_t(0x82) : uint8_t(lv.level())};
+                    store_pack<R, 1, NT>(sens + srow + X, kl);
+                    store_pack<R, 1, NT>(sens + (a.plane + srow) + X, neq);
+                    store_pack<R, 1, NT>(sens + (2 * a.plane + srow) + X, pi);
+                    store_pack<uint8_t, 1, NT>(flags + srow + X, fl);
+                }
             }
         }
         double sa, sb;
@@ -1415,7 +1422,10 @@ static hipError_t launch_pass(int pass, const D2Q9Args& a, const void* fin, void
             // extension sensors: F32 and F64 storage, whose pieces always stage
             if constexpr (std::is_same<S, float>::value || std::is_same<S, double>::value) {
                 if (!(LKS_D2Q9_LDS_STAGE && StageGeom<S, VEC>::ok)) return hipErrorInvalidValue;
-                d2q9_fused_lds<S, VEC, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, faults);
+                if (a.nt_stores)
+                    d2q9_fused_lds<S, VEC, true, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, faults);
+                else
+                    d2q9_fused_lds<S, VEC, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, faults);
             } else {
                 return hipErrorInvalidValue;
             }

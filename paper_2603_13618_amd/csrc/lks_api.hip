@@ -182,6 +182,7 @@ lks::D2Q25Args d2q25_args(const lks_config& c)
     a.thr_qe[1] = ddf(c) ? flag_thr_qe(c, 1) : INFINITY;
     a.aux = nullptr;
     a.nt_stores = 0;
+    a.quiet = 0;
     lks::d2q25_tile_shape(c.dtype, c.model, &a.tile_x, &a.tile_y);
     a.tiles_x = (c.nx + a.tile_x - 1) / a.tile_x;
     a.tiles_y = (c.ny + a.tile_y - 1) / a.tile_y;
@@ -190,10 +191,10 @@ lks::D2Q25Args d2q25_args(const lks_config& c)
 }
 
 // The tile form of a configuration's fused steps (0 = none): automatic launch
-// shapes only, without extension sensors.
+// shapes only.
 int tile_of(const lks_config& c)
 {
-    if (c.lattice != LKS_D2Q9 || c.ext_mask || c.launch_steps || c.launch_rows || c.launch_vec || c.launch_nt)
+    if (c.lattice != LKS_D2Q9 || c.launch_steps || c.launch_rows || c.launch_vec || c.launch_nt)
         return 0;
     return lks::d2q9_tile_of(c.dtype, c.nx, c.ny);
 }
@@ -291,6 +292,7 @@ struct lks_ctx {
     int nblocks_t;         // workgroups of the tile launches (a9.tile), else 0
     int slots_t;           // steps whose tile partial sums fit (1 .. kMaxChunk)
     bool single_t;         // single steps run in the tile form too
+    bool last_t;           // and a call's last step (it computes the extension sensors)
     double* partials;
     unsigned long long* faults;
     char err[kErrLen];     // fixed storage: reporting an error allocates nothing
@@ -406,6 +408,7 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
     c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0,
                                                   cfg.layout == LKS_LAYOUT_ROWS, vec == wide_vec(cfg.dtype));
+    c->last_t = c->single_t && !cfg.ext_mask;
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -448,8 +451,7 @@ int tile_part(const lks_ctx* c, int left)
 }
 
 // A batch of tile launches: as many of the call's `left` remaining steps as
-// one reduction launch can take, no single step that the row kernel does
-// better.  The sums of steps that a later step of the call overwrites are not
+// one reduction launch can take, no single step that belongs to the row kernel.  The sums of steps that a later step of the call overwrites are not
 // kept.  *taken = steps run (0: the next step belongs to the row kernel).
 lks_status tile_batch(lks_ctx* c, int left, int* taken)
 {
@@ -459,7 +461,7 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
         // of the launch's p steps, those among the call's last max_steps
         const int behind = left - m - c->cfg.max_steps;
         const int first = behind <= 0 ? 0 : (behind < p ? behind : p);
-        if ((p == 1 && !c->single_t) || kept + p - first > c->slots_t) break;
+        if ((p == 1 && !(left - m == 1 ? c->last_t : c->single_t)) || kept + p - first > c->slots_t) break;
         hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, c->a9, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
                                              c->buf.sensors, c->buf.flags,
                                              c->partials + (size_t)kept * c->nblocks_t * lks::kNsumsHost, first,
@@ -512,16 +514,22 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
             c->cur = 1 - c->cur;
         }
         for (int s = 0; !two && s < m; ++s) {
+            // steps whose sensors and flags the call's last step overwrites
+            const bool last = done + s == nsteps - 1;
             double* part = c->partials + (size_t)s * nb * lks::kNsumsHost;
             void* f = c->buf.pop[c->cur];
             void* g = c->buf.pop[1 - c->cur];
             hipError_t e;
             if (q25) {
-                e = lks::launch_d2q25(c->cfg.dtype, c->a25, f, g, c->buf.sensors, c->buf.flags, part,
+                lks::D2Q25Args q = c->a25;
+                q.quiet = last ? 0 : 1;
+                e = lks::launch_d2q25(c->cfg.dtype, q, f, g, c->buf.sensors, c->buf.flags, part,
                                       c->faults, c->stream);
                 if (e == hipSuccess) c->cur = 1 - c->cur;
             } else if (fused) {
-                e = lks::launch_d2q9(c->cfg.dtype, lks::kFused, a, f, g, c->buf.sensors,
+                lks::D2Q9Args q = a;
+                if (!last) q.x.mask = 0;        // the kernel without the extension sensors
+                e = lks::launch_d2q9(c->cfg.dtype, lks::kFused, q, f, g, c->buf.sensors,
                                      c->buf.flags, part, c->faults, c->stream);
                 if (e == hipSuccess) c->cur = 1 - c->cur;
             } else {
@@ -832,7 +840,7 @@ lks_status lks_step_from(lks_ctx* c, const void* src, void* dst)
     hipError_t e = c->cfg.lattice == LKS_D2Q25
                        ? lks::launch_d2q25(c->cfg.dtype, c->a25, src, dst, c->buf.sensors,
                                            c->buf.flags, c->partials, c->faults, c->stream)
-                   : c->single_t
+                   : c->last_t
                        ? lks::launch_d2q9_tile(c->cfg.dtype, c->a9, 1, src, dst, c->buf.sensors, c->buf.flags,
                                                c->partials, 0, c->faults, c->stream)
                        : lks::launch_d2q9(c->cfg.dtype, lks::kFused, c->a9, src, dst,

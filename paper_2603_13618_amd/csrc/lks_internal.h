@@ -88,6 +88,9 @@ struct D2Q25Args {
     // [6][plane] of drho, ux, uy, T - 1, q_g (x, y) in the compute type
     void* aux;
     int nt_stores;            // non-temporal population stores (large states)
+    // a step whose sensors and flags a later step of the same call overwrites:
+    // they are not stored, and its extension sensors not computed
+    int quiet;
 };
 constexpr int kDdfAux = 6;
 
@@ -108,7 +111,8 @@ int d2q9_two_blocks(int dtype, int nx, int ny);
 
 // k fused D2Q9 steps of each tile per launch (odd k <= steps of the tile form
 // a.tile); the partial sums of step j >= first go to partials + (j - first) *
-// blocks * kNsums, those of earlier steps nowhere
+// blocks * kNsums, those of earlier steps nowhere; sensors and flags are
+// written with k = 1 only
 hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                             uint8_t* flags, double* partials, int first, unsigned long long* faults,
                             hipStream_t s);

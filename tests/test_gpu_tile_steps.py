@@ -150,3 +150,50 @@ def test_captured_graph_replays():
         assert torch.equal(a.pop[cur], b.state) and torch.equal(a.sensors, b.sensors)
         assert torch.equal(a.flags, b.flags)
         np.testing.assert_allclose(a.sums.cpu().numpy()[:, 4:], b.sums.cpu().numpy()[:, 4:], rtol=1e-12)
+
+
+def _same_outputs(a, b):
+    torch.cuda.synchronize()
+    assert a.current() == b.current()
+    assert torch.equal(a.state, b.state)
+    assert torch.equal(a.sensors.view(torch.int64 if a.sensors.dtype == torch.float64 else torch.int32),
+                       b.sensors.view(torch.int64 if b.sensors.dtype == torch.float64 else torch.int32))
+    assert torch.equal(a.flags, b.flags)
+    assert a.check() == b.check()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny", [(40, 33), (300, 280), (563, 517)])
+def test_extension_sensors_of_the_last_step(dtype, nx, ny):
+    # computed in a call's last step only: the same bits as calls of one step
+    rho, ux, uy = inputs.random_state((ny, nx), 5, (0.95, 1.05), 0.05)
+    thr = np.full((lks.MAX_EXT, 2), np.inf)
+    thr[lks.EXT_NAMES.index("kn")] = (1e-3, 1e-2)
+    a, b = (lks.Lattice(9, nx, ny, dtype, tau=0.6, thr=THR, flag_mask=7 | lks.flag_x("kn"), max_steps=9,
+                        ext=("kn", "alpha", "strain"), thr_ext=thr) for _ in range(2))
+    for lat in (a, b):
+        lat.init(rho, ux, uy)
+    a.step(9)
+    for _ in range(9):
+        b.step(1)
+    _same_outputs(a, b)
+
+
+@pytest.mark.parametrize("ext", [None, ("kn", "qf")])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("model", ["bgk", "ddf"])
+def test_d2q25_sensors_of_the_last_step(model, dtype, ext):
+    nx, ny = 70, 45
+    rho, ux, uy, T, states = inputs.riemann_quadrants(nx, ny, seed=2)
+    dx = 1.0 / nx
+    kw = dict(model="ddf", gamma=1.4, prandtl=0.71) if model == "ddf" else {}
+    a, b = (lks.Lattice(25, nx, ny, dtype, mu=1e-3, dt=inputs.riemann_dt(states, dx), dx=dx, bc=(1, 1),
+                        thr=[[1e-6, 1e-4]] + [[1e-4, 1e-3]] * 3, flag_mask=15, max_steps=6, ext=ext, **kw)
+            for _ in range(2))
+    for lat in (a, b):
+        lat.init(rho, ux, uy, T)
+    a.step(6)
+    for _ in range(6):
+        b.step(1)
+    _same_outputs(a, b)
+    np.testing.assert_allclose(a.sums.cpu().numpy(), b.sums.cpu().numpy(), rtol=1e-12, atol=1e-300)
