@@ -406,6 +406,9 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
+    // FP64 extension sensors need two cells per thread: the call fails in its
+    // first step
+    if (cfg.ext_mask && cfg.dtype == LKS_F64 && vec == 1) a.tile = c->nblocks_t = c->slots_t = 0;
     c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0,
                                                   cfg.layout == LKS_LAYOUT_ROWS, vec == wide_vec(cfg.dtype));
     c->last_t = c->single_t && !cfg.ext_mask;

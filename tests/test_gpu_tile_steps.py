@@ -163,7 +163,7 @@ def _same_outputs(a, b):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
-@pytest.mark.parametrize("nx,ny", [(40, 33), (300, 280), (563, 517)])
+@pytest.mark.parametrize("nx,ny", [(40, 33), (300, 280), (564, 517)])
 def test_extension_sensors_of_the_last_step(dtype, nx, ny):
     # computed in a call's last step only: the same bits as calls of one step
     rho, ux, uy = inputs.random_state((ny, nx), 5, (0.95, 1.05), 0.05)
