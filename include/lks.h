@@ -347,6 +347,20 @@ lks_status lks_adjoint_step(lks_ctx* ctx, const void* pop_prev, const void* lam_
 lks_status lks_adjoint_init(lks_ctx* ctx, const double* rho0, const double* ux0,
                             const double* uy0, const void* lam0, double* gux, double* guy);
 
+/* Several steps per launch for the adjoint's trajectories (F32 or F64 storage;
+ * LKS_EUNSUPPORTED on grids too small for it, n = 0 asks).
+ *   trajectory: n steps from the state src, the state after step i + 1 into
+ *     dst[i], without sensors, flags, sums or fault count; the context's own
+ *     state and step count are not touched.  Steps run three per launch, the
+ *     last n mod 3 alone: dst[i] may be NULL (state not wanted) inside a
+ *     launch, not at its end (i mod 3 = 2, or i >= n - n mod 3).  dst[i] is
+ *     distinct from the launch's other buffers and its input.
+ *   steps: n = 1, 2 or 3 reverse steps (lks_adjoint_step) in one launch,
+ *     pop_prev[j] = the state before the j-th of them (newest first). */
+lks_status lks_trajectory(lks_ctx* ctx, const void* src, void* const* dst, int32_t n);
+lks_status lks_adjoint_steps(lks_ctx* ctx, const void* const* pop_prev, int32_t n, const void* lam_in,
+                             void* lam_out);
+
 lks_status lks_destroy(lks_ctx* ctx);
 
 const char* lks_status_str(lks_status s);

@@ -17,6 +17,7 @@
 // only the wave's edge lanes touch memory for it.  Pull streaming reads each
 // stored value exactly once, so HBM traffic is one read and one write per
 // population plus the sensor planes and the flag byte.
+#include "d2q9_band.h"
 #include "lks_device.h"
 #include "lks_internal.h"
 
@@ -85,7 +86,10 @@ template <typename R> struct CellSense {
 // of the pre-collision deviations d[0..8] in place.  EXT: also the extension
 // sensors into ext[0..kNumExt) (mu = tau rho c_s^2, lambda = 0 on this
 // isothermal lattice).
-template <typename R, bool SENSE, bool COLLIDE, bool EXT = false>
+// EXACT (without SENSE): the equilibrium goes to the collision through opaque
+// copies, as its other uses in the sensors would make it, so that the
+// post-collision state is the same bits as with SENSE.
+template <typename R, bool SENSE, bool COLLIDE, bool EXT = false, bool EXACT = false>
 __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau, R& drho_out,
                                                     R& jx_out, R& jy_out, R* ext = nullptr,
                                                     unsigned ext_mask = 0)
@@ -217,6 +221,10 @@ __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau
         }
     }
     if constexpr (COLLIDE) {
+        if constexpr (EXACT) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) deq[i] = pin(deq[i]);
+        }
 #pragma unroll
         for (int i = 0; i < 9; ++i) d[i] -= inv_tau * (d[i] - deq[i]);
     }
@@ -629,10 +637,6 @@ template <typename S, int TX, int TY, int K> struct TileSteps {
     static_assert(kTile % kWave == 0, "a wave reads whole rows of terms");
 };
 
-// Whether the tiles of T cells with a ring of K along an axis of n cells reach
-// at most one period beyond it on either side (what the kernels wrap).
-constexpr bool tile_fits(int n, int T, int K) { return n >= K && (n - 1) / T * T + T + K <= 2 * n; }
-
 // Sum of one value per lane over the wave, in lane 63: additions of the lanes
 // below within rows of 16 (DPP row shifts), then of the rows.
 template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v)
@@ -798,14 +802,6 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
 // us per step (the one-step row kernel in brackets): FP32 512^2 4.0 (17.5),
 // 1024^2 10.7 (17.9), 2048^2 36.5 (68.8), 4096^2 142 (239); FP64 1024^2 25.3
 // (33.6), 4096^2 356 (468); BF16 1024^2 10.9 (16.1), 4096^2 140 (178).
-template <typename S, int K, int NW> struct BandSteps {
-    using raw = typename Store<S>::raw;
-    using R = typename Store<S>::real;
-    static_assert(K == 1 || K == 3, "one or three steps");
-    static constexpr int TX = kWave, TY = 2 * NW, H0 = K - 1, W0 = TX + 2 * H0;
-    static constexpr int kCells = K == 1 ? 1 : W0 * (TY + 2 * H0);
-};
-
 // Sums over the wave of six values: halves, then 16-lane rows, of two values
 // are exchanged and added (each lane then carries one of them), then the rows
 // are added up.  Lane 0, 16, 32, 48 of `a`: values 0, 2, 1, 3; lane 0, 32 of
@@ -840,22 +836,21 @@ __device__ __forceinline__ void wave_sums6(const double (&v)[6], double& a, doub
     b = row_sum(swap_add16(r, r));
 }
 
-template <typename S, int K, int NW, bool NT>
-__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 ? 4 : 2))) void d2q9_band_kernel(
+template <typename S, int K, bool NT>
+__global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 ? 4 : 2))) void d2q9_band_kernel(
     D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
     typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
     int first, int nblocks, unsigned long long* __restrict__ faults)
 {
-    using G = BandSteps<S, K, NW>;
-    using R = typename G::R;
-    using raw = typename G::raw;
-    constexpr int TX = G::TX, TY = G::TY, H0 = G::H0, W0 = G::W0, C = G::kCells;
+    static_assert(K == 1 || K == 3, "one or three steps");
+    using G = Band<K>;
+    using R = typename Store<S>::real;
+    using raw = typename Store<S>::raw;
+    constexpr int NW = G::NW, TX = G::TX, TY = G::TY, W0 = G::W0, C = G::kCells;
     __shared__ raw buf[9 * C];
     __shared__ double red[K][NW][6];
 
-    // the XCD that runs a workgroup is its id mod 8: each takes runs of eight
-    // tiles along x
-    const int tile = blockIdx.x / 64 * 64 + blockIdx.x % 8 * 8 + blockIdx.x / 8 % 8;
+    const int tile = G::tile();
     if (tile >= nblocks) return;                    // whole workgroups
     const int nx = a.nx, ny = a.ny;
     const int tiles_x = (nx + TX - 1) / TX;
@@ -873,28 +868,10 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         th[s][1] = F32 ? R(a.thr_f[s][1]) : R(a.thr[s][1]);
     }
     unsigned nfault = 0;
-    // one period off at most (tile_fits)
-    auto wrap = [](int j, int n) {
-        j += j < 0 ? n : 0;
-        return j - (j >= n ? n : 0);
-    };
     unsigned xs[3];                                 // this lane's column and its neighbours
 #pragma unroll
-    for (int q = 0; q < 3; ++q) xs[q] = (unsigned)wrap(X0 + lane + q - 1, nx);
+    for (int q = 0; q < 3; ++q) xs[q] = (unsigned)G::wrap(X0 + lane + q - 1, nx);
 
-    // ring cell e of the ring of H cells: top and bottom rows, then the sides
-    auto ring_cell = [&](auto hc, int e, int& x, int& y) {
-        constexpr int H = decltype(hc)::value, W = TX + 2 * H;
-        if (e < 2 * H * W) {
-            const int r = e / W;
-            x = e - r * W - H;
-            y = r < H ? r - H : TY + r - H;
-        } else {
-            const int s = e - 2 * H * W, c = s % (2 * H);
-            x = c < H ? c - H : TX + c - H;
-            y = s / (2 * H);
-        }
-    };
     auto put = [&](int cell, const R (&d)[9]) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) buf[i * C + cell] = Store<S>::from_real(d[i]);
@@ -965,7 +942,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         for (int r = 0; r < 2; ++r) {
             static_for<9>([&](auto ic) {
                 constexpr int i = decltype(ic)::value;
-                const int ys = wrap(Y0 + 2 * wave + r - cy9(i), ny);
+                const int ys = G::wrap(Y0 + 2 * wave + r - cy9(i), ny);
                 d[r][i] = Store<S>::to_real((fin + a.L.at(i, ys, 0))[xs[1 - cx9(i)]]);
             });
         }
@@ -973,19 +950,17 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         int cell = 0;
         bool ring = false;
         if constexpr (K > 1) {
-            constexpr int n = (TX + 2 * H0) * (TY + 2 * H0) - TX * TY;
-            static_assert(n <= NW * kWave, "one ring cell a thread");
             int x, y;
-            ring = (int)threadIdx.x < n;
+            ring = (int)threadIdx.x < G::template ring<G::H0>();
             if (ring) {
-                ring_cell(std::integral_constant<int, H0>{}, threadIdx.x, x, y);
-                cell = (y + H0) * W0 + x + H0;
+                G::template ring_cell<G::H0>(threadIdx.x, x, y);
+                cell = G::cell(x, y);
                 long long row[3];
                 int col[3];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    row[q] = (long long)wrap(Y0 + y + q - 1, ny) * a.L.pr;
-                    col[q] = wrap(X0 + x + q - 1, nx);
+                    row[q] = (long long)G::wrap(Y0 + y + q - 1, ny) * a.L.pr;
+                    col[q] = G::wrap(X0 + x + q - 1, nx);
                 }
 #pragma unroll
                 for (int i = 0; i < 9; ++i)
@@ -994,8 +969,8 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         }
         owned(0, d, K == 1);
         if constexpr (K > 1) {
-            put((2 * wave + H0) * W0 + lane + H0, d[0]);
-            put((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            put(G::cell(lane, 2 * wave), d[0]);
+            put(G::cell(lane, 2 * wave + 1), d[1]);
             if (ring) {
                 ring_update(g);
                 put(cell, g);
@@ -1007,30 +982,29 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         {   // ---- step 1: in place
             R d[2][9], g[9];
             int cell = 0;
-            constexpr int n = (TX + 2) * (TY + 2) - TX * TY;
             // the ring goes to the waves that had none, or less, of step 0's
             const int e = NW * kWave - 1 - (int)threadIdx.x;
-            const bool ring = e < n;
-            get((2 * wave + H0) * W0 + lane + H0, d[0]);
-            get((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            const bool ring = e < G::template ring<1>();
+            get(G::cell(lane, 2 * wave), d[0]);
+            get(G::cell(lane, 2 * wave + 1), d[1]);
             owned(1, d, false);
             if (ring) {
                 int x, y;
-                ring_cell(std::integral_constant<int, 1>{}, e, x, y);
-                cell = (y + H0) * W0 + x + H0;
+                G::template ring_cell<1>(e, x, y);
+                cell = G::cell(x, y);
                 get(cell, g);
                 ring_update(g);
             }
             __syncthreads();
-            put((2 * wave + H0) * W0 + lane + H0, d[0]);
-            put((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            put(G::cell(lane, 2 * wave), d[0]);
+            put(G::cell(lane, 2 * wave + 1), d[1]);
             if (ring) put(cell, g);
         }
         __syncthreads();
         {   // ---- step 2: to global memory
             R d[2][9];
-            get((2 * wave + H0) * W0 + lane + H0, d[0]);
-            get((2 * wave + 1 + H0) * W0 + lane + H0, d[1]);
+            get(G::cell(lane, 2 * wave), d[0]);
+            get(G::cell(lane, 2 * wave + 1), d[1]);
             owned(2, d, true);
         }
         __syncthreads();
@@ -1045,6 +1019,140 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(size
         if (j >= first) partials[((long long)(j - first) * nblocks + tile) * kNsums + k] = s;
     }
     if (nfault) atomicAdd(faults, (unsigned long long)nfault);
+}
+
+// K steps of the state alone (no sensors, flags, sums or fault count), as the
+// adjoint replays a trajectory: the band kernel's geometry and staging, each
+// step's state stored where the caller wants it (out0, out1: null to skip).
+// HBM-bound with every state stored (FP32 1024^2: 12 B read + 36 B written per
+// cell and step), VALU-bound with the last one only.
+template <typename S, int K>
+__global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
+    D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ out0,
+    typename Store<S>::raw* __restrict__ out1, typename Store<S>::raw* __restrict__ out2, int ntiles)
+{
+    static_assert(K == 1 || K == 3, "one or three steps");
+    using G = Band<K>;
+    using R = typename Store<S>::real;
+    using raw = typename Store<S>::raw;
+    constexpr int W0 = G::W0, C = G::kCells;
+    __shared__ raw buf[9 * C];
+
+    const int tile = G::tile();
+    if (tile >= ntiles) return;                     // whole workgroups
+    const int nx = a.nx, ny = a.ny;
+    const int tiles_x = (nx + G::TX - 1) / G::TX;
+    const int X0 = (tile % tiles_x) * G::TX, Y0 = (tile / tiles_x) * G::TY;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    constexpr bool F32 = sizeof(R) == 4;
+    const R rho0 = F32 ? R(a.rho0_f) : R(a.rho0);
+    const R inv_tau = F32 ? R(a.inv_tau_f) : R(1.0 / a.tau);
+    unsigned xs[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) xs[q] = (unsigned)G::wrap(X0 + lane + q - 1, nx);
+
+    auto put = [&](int cell, const R (&d)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) buf[i * C + cell] = Store<S>::from_real(d[i]);
+    };
+    auto get = [&](int cell, R (&d)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) d[i] = Store<S>::to_real(buf[i * C + cell - cy9(i) * W0 - cx9(i)]);
+    };
+    auto step = [&](R (&d)[9]) {
+        R drho, jx, jy;
+        (void)cell_update<R, false, true, false, true>(d, rho0, inv_tau, drho, jx, jy);
+    };
+    auto store = [&](raw* out, const R (&d)[2][9]) {
+        if (!out || X0 + lane >= nx) return;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int Y = Y0 + 2 * wave + r;
+            if (Y >= ny) break;
+            const long long prow = a.L.at(0, Y, 0);
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                (out + (prow + i * a.L.pp))[(unsigned)(X0 + lane)] = Store<S>::from_real(d[r][i]);
+        }
+    };
+
+    {   // ---- step 0: from global memory
+        R d[2][9], g[9];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            static_for<9>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                const int ys = G::wrap(Y0 + 2 * wave + r - cy9(i), ny);
+                d[r][i] = Store<S>::to_real((fin + a.L.at(i, ys, 0))[xs[1 - cx9(i)]]);
+            });
+        }
+        const bool ring = K > 1 && (int)threadIdx.x < G::template ring<G::H0>();
+        int cell = 0;
+        if constexpr (K > 1) {
+            if (ring) {
+                int x, y;
+                G::template ring_cell<G::H0>(threadIdx.x, x, y);
+                cell = G::cell(x, y);
+                long long row[3];
+                int col[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    row[q] = (long long)G::wrap(Y0 + y + q - 1, ny) * a.L.pr;
+                    col[q] = G::wrap(X0 + x + q - 1, nx);
+                }
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    g[i] = Store<S>::to_real(fin[i * a.L.pp + row[1 - cy9(i)] + col[1 - cx9(i)]]);
+            }
+        }
+        step(d[0]);
+        step(d[1]);
+        store(out0, d);
+        if constexpr (K > 1) {
+            put(G::cell(lane, 2 * wave), d[0]);
+            put(G::cell(lane, 2 * wave + 1), d[1]);
+            if (ring) {
+                step(g);
+                put(cell, g);
+            }
+        }
+    }
+    if constexpr (K > 1) {
+        __syncthreads();
+        {   // ---- step 1: in place
+            R d[2][9], g[9];
+            int cell = 0;
+            // the ring goes to the waves that had none, or less, of step 0's
+            const int e = G::NW * kWave - 1 - (int)threadIdx.x;
+            const bool ring = e < G::template ring<1>();
+            get(G::cell(lane, 2 * wave), d[0]);
+            get(G::cell(lane, 2 * wave + 1), d[1]);
+            step(d[0]);
+            step(d[1]);
+            if (ring) {
+                int x, y;
+                G::template ring_cell<1>(e, x, y);
+                cell = G::cell(x, y);
+                get(cell, g);
+                step(g);
+            }
+            store(out1, d);
+            __syncthreads();
+            put(G::cell(lane, 2 * wave), d[0]);
+            put(G::cell(lane, 2 * wave + 1), d[1]);
+            if (ring) put(cell, g);
+        }
+        __syncthreads();
+        {   // ---- step 2: to global memory
+            R d[2][9];
+            get(G::cell(lane, 2 * wave), d[0]);
+            get(G::cell(lane, 2 * wave + 1), d[1]);
+            step(d[0]);
+            step(d[1]);
+            store(out2, d);
+        }
+    }
 }
 
 // Two fused steps per pass over HBM (temporal blocking): the API keeps
@@ -1289,9 +1397,6 @@ static hipError_t launch_tile_steps(const D2Q9Args& a, int k, const void* fin, v
     return hipGetLastError();
 }
 
-constexpr int kBandWaves = 8;
-constexpr int kBandX = kWave, kBandY = 2 * kBandWaves, kBandK = 3;
-
 template <typename S>
 static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                                     uint8_t* flags, double* partials, int first, unsigned long long* faults,
@@ -1299,11 +1404,9 @@ static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, v
 {
     using raw = typename Store<S>::raw;
     using R = typename Store<S>::real;
-    constexpr int NW = kBandWaves;
-    if ((k != 1 && k != 3) || !tile_fits(a.nx, kBandX, kBandK) || !tile_fits(a.ny, kBandY, kBandK))
-        return hipErrorInvalidValue;
-    const int n = ((a.nx + kBandX - 1) / kBandX) * ((a.ny + kBandY - 1) / kBandY);
-    const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(NW * kWave);
+    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
+    const int n = band_tiles(a.nx, a.ny);
+    const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
     // The non-temporal hint where rows are whole half lines only: partial
     // lines that leave the cache early are written twice (a step alone, plain /
     // hint: FP32 5000 x 4000 363 / 454 us, BF16 235 / 333; FP32 4016 x 3000 203 /
@@ -1313,14 +1416,40 @@ static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, v
     raw* out = (raw*)fout;
     R* sv = (R*)sens;
     if (k == 3 && nt)
-        d2q9_band_kernel<S, 3, NW, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 3, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else if (k == 3)
-        d2q9_band_kernel<S, 3, NW, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 3, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else if (nt)
-        d2q9_band_kernel<S, 1, NW, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 1, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else
-        d2q9_band_kernel<S, 1, NW, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 1, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     return hipGetLastError();
+}
+
+template <typename S>
+static hipError_t launch_state(const D2Q9Args& a, int k, const void* fin, void* const* out, hipStream_t st)
+{
+    using raw = typename Store<S>::raw;
+    const int n = band_tiles(a.nx, a.ny);
+    const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
+    if (k == 3)
+        d2q9_band_state_kernel<S, 3><<<grid, block, 0, st>>>(a, (const raw*)fin, (raw*)out[0], (raw*)out[1],
+                                                             (raw*)out[2], n);
+    else
+        d2q9_band_state_kernel<S, 1><<<grid, block, 0, st>>>(a, (const raw*)fin, (raw*)out[0], nullptr, nullptr, n);
+    return hipGetLastError();
+}
+
+bool d2q9_band_fits(int nx, int ny) { return band_fits(nx, ny); }
+
+hipError_t launch_d2q9_state(int dtype, const D2Q9Args& a, int k, const void* fin, void* const* out, hipStream_t s)
+{
+    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
+    switch (dtype) {
+    case 0: return launch_state<double>(a, k, fin, out, s);
+    case 1: return launch_state<float>(a, k, fin, out, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 // Tile forms (F(form, columns, rows, most steps)): the tile kernel's three,
@@ -1343,7 +1472,7 @@ int d2q9_tile_of(int dtype, int nx, int ny)
         return V;
     LKS_TILE_FORMS(LKS_TILE_FITS)
 #undef LKS_TILE_FITS
-    if (tile_fits(nx, kBandX, kBandK) && tile_fits(ny, kBandY, kBandK)) return kBandForm;
+    if (band_fits(nx, ny)) return kBandForm;
     if (dtype != 0 && tile_fits(nx, 32, 5) && tile_fits(ny, 16, 5)) return 3;
     if (tile_fits(nx, 16, 7) && tile_fits(ny, 16, 7)) return 2;
     return tile_fits(nx, 8, 7) && tile_fits(ny, 8, 7) ? 1 : 0;
@@ -1366,7 +1495,7 @@ int d2q9_tile_blocks(int tile, int nx, int ny)
 #define LKS_TILE_BLOCKS(V, TX, TY, K) case V: return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
     LKS_TILE_FORMS(LKS_TILE_BLOCKS)
 #undef LKS_TILE_BLOCKS
-    case kBandForm: return ((nx + kBandX - 1) / kBandX) * ((ny + kBandY - 1) / kBandY);
+    case kBandForm: return band_tiles(nx, ny);
     default: return 0;
     }
 }

@@ -20,6 +20,7 @@
 // Each reverse step reads the previous state (pulled by -c), the incoming
 // adjoint (pulled by +c) and writes the outgoing adjoint: no atomics, every
 // output written once.
+#include "d2q9_band.h"
 #include "lks_device.h"
 #include "lks_internal.h"
 
@@ -112,18 +113,12 @@ __global__ __launch_bounds__(kBlock) void adj_seed_kernel(int nx, int ny, long l
         lam[L.at(j, y, x)] = lnr[j] - (bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)) / rho;
 }
 
+// one cell of the reverse step: J_C(g)^T l from the pulled state d (g_i = w_i
+// rho0 + d_i) and the pulled adjoint l
 template <typename R>
-__global__ __launch_bounds__(kBlock) void adj_step_kernel(int nx, int ny, long long plane, PopLayout L, R rho0, R tau,
-                                                     const R* __restrict__ fprev,
-                                                     const R* __restrict__ lam_in,
-                                                     R* __restrict__ lam_out)
+__device__ __forceinline__ void collide_adjoint(const R (&d)[9], const R (&l)[9], R rho0, R tau, R (&out)[9])
 {
-    const long long c = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= plane) return;
-    const int x = (int)(c % nx), y = (int)(c / nx);
-    R d[9], l[9], drho, rho, ux, uy;
-    pull9<1>(fprev, L, x, y, nx, ny, d);
-    pull9<-1>(lam_in, L, x, y, nx, ny, l);
+    R drho, rho, ux, uy;
     cell_moments(d, rho0, drho, rho, ux, uy);
     const R usq = ux * ux + uy * uy;
     R a0 = R(0), bx = R(0), by = R(0);
@@ -139,8 +134,136 @@ __global__ __launch_bounds__(kBlock) void adj_step_kernel(int nx, int ny, long l
     const R it = R(1) / tau;
 #pragma unroll
     for (int j = 0; j < 9; ++j)
-        lam_out[L.at(j, y, x)] =
-            (R(1) - it) * l[j] + it * (a0 + (bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)) / rho);
+        out[j] = (R(1) - it) * l[j] + it * (a0 + (bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)) / rho);
+}
+
+template <typename R>
+__global__ __launch_bounds__(kBlock) void adj_step_kernel(int nx, int ny, long long plane, PopLayout L, R rho0, R tau,
+                                                     const R* __restrict__ fprev,
+                                                     const R* __restrict__ lam_in,
+                                                     R* __restrict__ lam_out)
+{
+    const long long c = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (c >= plane) return;
+    const int x = (int)(c % nx), y = (int)(c / nx);
+    R d[9], l[9], out[9];
+    pull9<1>(fprev, L, x, y, nx, ny, d);
+    pull9<-1>(lam_in, L, x, y, nx, ny, l);
+    collide_adjoint(d, l, rho0, tau, out);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) lam_out[L.at(j, y, x)] = out[j];
+}
+
+// K reverse steps of a band tile per launch, on the geometry of the forward
+// band kernel: the incoming adjoint is read once (the tile and a ring of K
+// cells), each later step takes the one before it from LDS (in place: results
+// are held in registers across a barrier), and each step reads the state
+// before it, pulled, from global memory.  The arithmetic is collide_adjoint's,
+// so the result is that of K one-step launches.  Per cell and step K = 3 moves
+// 36 + 24 B (FP32) where a step alone moves 108.
+template <typename R, int K>
+__global__ __launch_bounds__(kBandWaves * kWave) void adj_band_kernel(D2Q9Args a, R rho0, R tau,
+                                                                     const R* __restrict__ f0,
+                                                                     const R* __restrict__ f1,
+                                                                     const R* __restrict__ f2,
+                                                                     const R* __restrict__ lam_in,
+                                                                     R* __restrict__ lam_out, int ntiles)
+{
+    using G = Band<K>;
+    constexpr int W0 = G::W0, C = G::kCells;
+    __shared__ R buf[9 * C];
+    const int tile = G::tile();
+    if (tile >= ntiles) return;                     // whole workgroups
+    const int nx = a.nx, ny = a.ny;
+    const int tiles_x = (nx + G::TX - 1) / G::TX;
+    const int X0 = (tile % tiles_x) * G::TX, Y0 = (tile / tiles_x) * G::TY;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    unsigned xs[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) xs[q] = (unsigned)G::wrap(X0 + lane + q - 1, nx);
+
+    // row r of this wave: population i at (x - SIGN c_i) of f
+    auto pull_row = [&](auto sc, const R* f, int r, R (&v)[9]) {
+        constexpr int SIGN = decltype(sc)::value;
+        sfor<9>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const int ys = G::wrap(Y0 + 2 * wave + r - SIGN * acy(i), ny);
+            v[i] = (f + a.L.at(i, ys, 0))[xs[1 - SIGN * acx(i)]];
+        });
+    };
+    auto pull_cell = [&](auto sc, const R* f, int x, int y, R (&v)[9]) {
+        constexpr int SIGN = decltype(sc)::value;
+        long long row[3];
+        int col[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            row[q] = (long long)G::wrap(Y0 + y + q - 1, ny) * a.L.pr;
+            col[q] = G::wrap(X0 + x + q - 1, nx);
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) v[i] = f[i * a.L.pp + row[1 - SIGN * acy(i)] + col[1 - SIGN * acx(i)]];
+    };
+    auto put = [&](int cell, const R (&v)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) buf[i * C + cell] = v[i];
+    };
+    // the adjoint of streaming: population i at x + c_i
+    auto get = [&](int cell, R (&v)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) v[i] = buf[i * C + cell + acy(i) * W0 + acx(i)];
+    };
+    const std::integral_constant<int, 1> fwd;
+    const std::integral_constant<int, -1> bwd;
+
+    // one step: H = cells of the ring it produces; the first reads lam_in, the
+    // last writes lam_out
+    auto step = [&](auto hc, const R* f) {
+        constexpr int H = decltype(hc)::value;
+        constexpr bool first = H == K - 1, last = H == 0;
+        // the first step's ring goes to the low threads, the next one's to the high
+        const int e = first ? (int)threadIdx.x : G::NW * kWave - 1 - (int)threadIdx.x;
+        const bool ring = e < G::template ring<H>();
+        R out[2][9], og[9];
+        int cell = 0;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            R d[9], l[9];
+            pull_row(fwd, f, r, d);
+            if constexpr (first) pull_row(bwd, lam_in, r, l);
+            else get(G::cell(lane, 2 * wave + r), l);
+            collide_adjoint(d, l, rho0, tau, out[r]);
+        }
+        if constexpr (!last) {
+            if (ring) {
+                int x, y;
+                G::template ring_cell<H>(e, x, y);
+                cell = G::cell(x, y);
+                R d[9], l[9];
+                pull_cell(fwd, f, x, y, d);
+                if constexpr (first) pull_cell(bwd, lam_in, x, y, l);
+                else get(cell, l);
+                collide_adjoint(d, l, rho0, tau, og);
+            }
+            if constexpr (!first) __syncthreads();
+            put(G::cell(lane, 2 * wave), out[0]);
+            put(G::cell(lane, 2 * wave + 1), out[1]);
+            if (ring) put(cell, og);
+            __syncthreads();
+        } else if (X0 + lane < nx) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int Y = Y0 + 2 * wave + r;
+                if (Y >= ny) break;
+                const long long prow = a.L.at(0, Y, 0);
+#pragma unroll
+                for (int i = 0; i < 9; ++i) (lam_out + (prow + i * a.L.pp))[(unsigned)(X0 + lane)] = out[r][i];
+            }
+        }
+    };
+    step(std::integral_constant<int, K - 1>{}, f0);
+    if constexpr (K == 3) step(std::integral_constant<int, 1>{}, f1);
+    step(std::integral_constant<int, 0>{}, K == 3 ? f2 : f1);
 }
 
 template <typename R>
@@ -201,6 +324,30 @@ hipError_t launch_adj_step(int dtype, const D2Q9Args& a, const void* pop_prev, c
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+template <typename R>
+static hipError_t launch_adj_band(const D2Q9Args& a, int k, const void* const* f, const void* lam_in, void* lam_out,
+                                  hipStream_t s)
+{
+    const int n = band_tiles(a.nx, a.ny);
+    const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
+    if (k == 3)
+        adj_band_kernel<R, 3><<<grid, block, 0, s>>>(a, R(a.rho0), R(a.tau), (const R*)f[0], (const R*)f[1],
+                                                     (const R*)f[2], (const R*)lam_in, (R*)lam_out, n);
+    else
+        adj_band_kernel<R, 2><<<grid, block, 0, s>>>(a, R(a.rho0), R(a.tau), (const R*)f[0], (const R*)f[1],
+                                                     nullptr, (const R*)lam_in, (R*)lam_out, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_steps(int dtype, const D2Q9Args& a, int k, const void* const* pop_prev, const void* lam_in,
+                            void* lam_out, hipStream_t s)
+{
+    if ((k != 2 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
+    if (dtype == 0) return launch_adj_band<double>(a, k, pop_prev, lam_in, lam_out, s);
+    if (dtype == 1) return launch_adj_band<float>(a, k, pop_prev, lam_in, lam_out, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_adj_init(int dtype, const D2Q9Args& a, const double* rho0, const double* ux0,

@@ -885,6 +885,54 @@ lks_status lks_adjoint_step(lks_ctx* c, const void* pop_prev, const void* lam_in
                      "adjoint step kernel");
 }
 
+lks_status lks_trajectory(lks_ctx* c, const void* src, void* const* dst, int32_t n)
+{
+    if (!c) return LKS_EINVAL;
+    if (lks_status s = adjoint_ok(c)) return s;
+    if (!lks::d2q9_band_fits(c->cfg.nx, c->cfg.ny))
+        return fail(c, LKS_EUNSUPPORTED, "the grid is too small for several steps per launch");
+    if (n < 0) return fail(c, LKS_EINVAL, "n must be >= 0");
+    if (n == 0) return LKS_OK;
+    if (!src || !dst) return fail(c, LKS_EINVAL, "src and dst are required");
+    // every launch's buffers before the first launch
+    for (int i = 0; i < n;) {
+        const int k = n - i >= 3 ? 3 : 1;
+        const void* in = i ? dst[i - 1] : src;
+        for (int j = 0; j < k; ++j) {
+            if (!dst[i + j] && j == k - 1) return fail(c, LKS_EINVAL, "dst[%d] is required", i + j);
+            for (int m = 0; m < j; ++m)
+                if (dst[i + j] && dst[i + j] == dst[i + m]) return fail(c, LKS_EINVAL, "dst[%d] aliases another", i + j);
+            if (dst[i + j] == in) return fail(c, LKS_EINVAL, "dst[%d] aliases the state it is computed from", i + j);
+        }
+        i += k;
+    }
+    for (int i = 0; i < n;) {
+        const int k = n - i >= 3 ? 3 : 1;
+        hipError_t e = lks::launch_d2q9_state(c->cfg.dtype, c->a9, k, i ? dst[i - 1] : src, dst + i, c->stream);
+        if (lks_status s = hip_check(c, e, "state kernel")) return s;
+        i += k;
+    }
+    return LKS_OK;
+}
+
+lks_status lks_adjoint_steps(lks_ctx* c, const void* const* pop_prev, int32_t n, const void* lam_in, void* lam_out)
+{
+    if (!c) return LKS_EINVAL;
+    if (lks_status s = adjoint_ok(c)) return s;
+    if (n < 1 || n > 3) return fail(c, LKS_EINVAL, "n must be 1, 2 or 3");
+    if (n > 1 && !lks::d2q9_band_fits(c->cfg.nx, c->cfg.ny))
+        return fail(c, LKS_EUNSUPPORTED, "the grid is too small for several steps per launch");
+    if (!pop_prev || !lam_in || !lam_out) return fail(c, LKS_EINVAL, "pop_prev, lam_in and lam_out are required");
+    if (lam_in == lam_out) return fail(c, LKS_EINVAL, "lam_out must not alias an input");
+    for (int i = 0; i < n; ++i) {
+        if (!pop_prev[i]) return fail(c, LKS_EINVAL, "pop_prev[%d] is required", i);
+        if (pop_prev[i] == lam_out) return fail(c, LKS_EINVAL, "lam_out must not alias an input");
+    }
+    hipError_t e = n == 1 ? lks::launch_adj_step(c->cfg.dtype, c->a9, pop_prev[0], lam_in, lam_out, c->stream)
+                          : lks::launch_adj_steps(c->cfg.dtype, c->a9, n, pop_prev, lam_in, lam_out, c->stream);
+    return hip_check(c, e, "adjoint steps kernel");
+}
+
 lks_status lks_adjoint_init(lks_ctx* c, const double* rho0, const double* ux0, const double* uy0,
                             const void* lam0, double* gux, double* guy)
 {

@@ -163,6 +163,15 @@ hipError_t launch_finalize(double* partials, int nblocks, int nsteps, double* su
                            long long row0, int max_rows, double mass_ref, double energy_ref,
                            hipStream_t s);
 
+// The adjoint's replay (D2Q9, F32/F64 storage): k = 1 or 3 steps of the state
+// alone, step j's state to out[j] (with k = 3 out[0] and out[1] may be null).
+// Needs d2q9_band_fits, as launch_adj_steps does.
+bool d2q9_band_fits(int nx, int ny);
+hipError_t launch_d2q9_state(int dtype, const D2Q9Args& a, int k, const void* fin, void* const* out, hipStream_t s);
+// k = 2 or 3 adjoint steps in one launch; pop_prev[j]: the state before step j's
+hipError_t launch_adj_steps(int dtype, const D2Q9Args& a, int k, const void* const* pop_prev, const void* lam_in,
+                            void* lam_out, hipStream_t s);
+
 // adjoint kernels (D2Q9, F32/F64 storage)
 hipError_t launch_adj_seed(int dtype, const D2Q9Args& a, const void* pop_prev, void* lam_out,
                            hipStream_t s);

@@ -119,6 +119,8 @@ def lib():
             "lks_check": ([P, ctypes.POINTER(I64)], I32),
             "lks_adjoint_seed_kl": ([P, P, P], I32),
             "lks_adjoint_step": ([P, P, P, P], I32),
+            "lks_trajectory": ([P, P, ctypes.POINTER(P), I32], I32),
+            "lks_adjoint_steps": ([P, ctypes.POINTER(P), I32, P, P], I32),
             "lks_adjoint_init": ([P, P, P, P, P, P, P], I32),
             "lks_destroy": ([P], I32),
             "lks_status_str": ([I32], ctypes.c_char_p),
@@ -392,6 +394,27 @@ class Lattice:
         _check(lib().lks_adjoint_step(self.ctx, self._state_arg(pop_prev, "pop_prev"),
                                       self._state_arg(lam_in, "lam_in"),
                                       self._state_arg(lam_out, "lam_out")), self.ctx)
+
+    def has_trajectory(self):
+        """Whether trajectory() and adjoint_steps() of several steps take this grid."""
+        return lib().lks_trajectory(self.ctx, None, None, 0) == 0
+
+    def _state_args(self, states, what):
+        return (ctypes.c_void_p * max(len(states), 1))(
+            *[None if t is None else self._state_arg(t, what).value for t in states])
+
+    def trajectory(self, src, dst):
+        """len(dst) steps from the state tensor src, the state after step i + 1 into
+        dst[i] (None inside a launch of three steps: not stored)."""
+        _check(lib().lks_trajectory(self.ctx, self._state_arg(src, "src"), self._state_args(dst, "dst"),
+                                    len(dst)), self.ctx)
+
+    def adjoint_steps(self, pop_prev, lam_in, lam_out):
+        """One to three reverse steps in one launch; pop_prev: the states before
+        them, newest first."""
+        _check(lib().lks_adjoint_steps(self.ctx, self._state_args(pop_prev, "pop_prev"), len(pop_prev),
+                                       self._state_arg(lam_in, "lam_in"),
+                                       self._state_arg(lam_out, "lam_out")), self.ctx)
 
     def adjoint_init(self, rho0, ux0, uy0, lam0, gux, guy):
         _check(lib().lks_adjoint_init(self.ctx, _ptr(rho0), _ptr(ux0), _ptr(uy0),
