@@ -67,7 +67,7 @@ __device__ __forceinline__ void pull9(const R* __restrict__ f, const PopLayout& 
 
 // moments of a cell from its stored deviations d_i = f_i - w_i rho0
 template <typename R>
-__device__ __forceinline__ void cell_moments(const R (&d)[9], R rho0, R& drho, R& rho, R& ux, R& uy)
+__device__ __forceinline__ Divisor<R> cell_moments(const R (&d)[9], R rho0, R& drho, R& rho, R& ux, R& uy)
 {
     R jx = R(0), jy = R(0);
     drho = R(0);
@@ -78,8 +78,10 @@ __device__ __forceinline__ void cell_moments(const R (&d)[9], R rho0, R& drho, R
         jy += R(acy(i)) * d[i];
     }
     rho = rho0 + drho;
-    ux = jx / rho;
-    uy = jy / rho;
+    const Divisor<R> by_rho(rho);
+    ux = by_rho.of(jx);
+    uy = by_rho.of(jy);
+    return by_rho;
 }
 
 template <typename R>
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(kBlock) void adj_seed_kernel(int nx, int ny, long l
     const int x = (int)(c % nx), y = (int)(c / nx);
     R d[9], drho, rho, ux, uy;
     pull9<1>(fprev, L, x, y, nx, ny, d);
-    cell_moments(d, rho0, drho, rho, ux, uy);
+    const Divisor<R> by_rho = cell_moments(d, rho0, drho, rho, ux, uy);
     const R usq15 = R(1.5) * (ux * ux + uy * uy);
     // with x_i = f^neq_i / f^eq_i: g_i / f^eq_i = 1 + x_i, and the "1" part of
     // B'_a vanishes because sum_i w_i dP_i/du_a = 0
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void adj_seed_kernel(int nx, int ny, long l
     }
 #pragma unroll
     for (int j = 0; j < 9; ++j)
-        lam[L.at(j, y, x)] = lnr[j] - (bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)) / rho;
+        lam[L.at(j, y, x)] = lnr[j] - by_rho.of(bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy));
 }
 
 // one cell of the reverse step: J_C(g)^T l from the pulled state d (g_i = w_i
@@ -119,7 +121,7 @@ template <typename R>
 __device__ __forceinline__ void collide_adjoint(const R (&d)[9], const R (&l)[9], R rho0, R tau, R (&out)[9])
 {
     R drho, rho, ux, uy;
-    cell_moments(d, rho0, drho, rho, ux, uy);
+    const Divisor<R> by_rho = cell_moments(d, rho0, drho, rho, ux, uy);
     const R usq = ux * ux + uy * uy;
     R a0 = R(0), bx = R(0), by = R(0);
 #pragma unroll
@@ -134,7 +136,7 @@ __device__ __forceinline__ void collide_adjoint(const R (&d)[9], const R (&l)[9]
     const R it = R(1) / tau;
 #pragma unroll
     for (int j = 0; j < 9; ++j)
-        out[j] = (R(1) - it) * l[j] + it * (a0 + (bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)) / rho);
+        out[j] = (R(1) - it) * l[j] + it * (a0 + by_rho.of(bx * (R(acx(j)) - ux) + by * (R(acy(j)) - uy)));
 }
 
 template <typename R>

@@ -194,7 +194,31 @@ __device__ __forceinline__ void store_pack(T* __restrict__ p, const T (&in)[VEC]
 // Arithmetic helpers
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+// FP64: the hardware estimate, two Newton steps and a last residual step, as
+// the compiler's division does without its range scaling (7 instructions
+// instead of 11): 1/x correctly rounded for normal x and 1/x.  Zero, infinite
+// and subnormal x give NaN or infinity; they only occur in cells that are
+// positivity faults whatever the value.
+__device__ __forceinline__ double rcp(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// Quotients by one divisor: its reciprocal once, then each quotient with a
+// residual correction, which rounds it correctly (quotients in the normal
+// range) in three instructions instead of a division's ten.
+template <typename R> struct Divisor {
+    R x, r;
+    __device__ __forceinline__ explicit Divisor(R v) : x(v), r(rcp(v)) { r = fma(fma(-x, r, R(1)), r, r); }
+    __device__ __forceinline__ R of(R n) const
+    {
+        const R q = n * r;
+        return fma(fma(-x, q, n), r, q);
+    }
+};
 __device__ __forceinline__ float log1p_r(float x) { return log1pf(x); }
 __device__ __forceinline__ double log1p_r(double x) { return log1p(x); }
 
