@@ -786,26 +786,29 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
 
 // Three steps of one tile per launch, mid-size and large grids.  A one-step
 // kernel moves 85 B per cell and step (FP32) and waits for HBM; three steps
-// for one pass leave the VALU issue as the bound.  A workgroup of NW waves owns
-// 64 columns and 2 NW rows, two rows a wave, one lane a column.  Step 0 reads
+// for one pass leave the VALU issue as the bound.  A workgroup of eight waves
+// owns 64 columns and 8 NR rows, NR rows a wave, one lane a column.  Step 0 reads
 // its populations from global memory (the tile and a ring of two cells, whose
 // cells are dealt out densely over the waves) and writes the post-collision
 // values, rounded to the storage type, to LDS; step 1 (the tile and a ring of
 // one cell) reads them, holds its results in registers across a barrier and
-// writes them in their place; step 2 stores the state.  In place, the 68 x 20 cells take 49 KB in FP32, so that several workgroups share
-// a CU and one's loads and stores hide behind another's arithmetic.  K = 1: a
-// single step on the same tiles, so that every step's sums are added in the
-// same order whichever launch it runs in.  Cell arithmetic: cell_update.
-// Eight waves: 57 wave updates for the 48 that the tile itself needs; six waves
-// (64 x 12 tiles) and sixteen (64 x 32, one workgroup a CU) measured 204 and 179
-// against 142 us per step at FP32 4096^2.
+// writes them in their place; step 2 stores the state.  In place, the 68 x 20
+// (NR = 2) or 68 x 28 cells take 49 or 69 KB in FP32, so that two workgroups
+// share a CU and one's loads and stores hide behind the other's arithmetic.
+// K = 1: a single step on the same tiles, so that every step's sums are added
+// in the same order whichever launch it runs in.  Cell arithmetic:
+// cell_update (246 VALU instructions, of which ring cells need 100).  A row's
+// sums cost 88 instructions with a reduction of each of the six values; what
+// is left after sharing it (wave_sums6), keeping lanes outside the grid out of
+// it only where there are any, and counting faults by ballot took 142 to 129 us
+// per step at FP32 4096^2, NR = 2.
 // us per step (the one-step row kernel in brackets): FP32 512^2 4.0 (17.5),
-// 1024^2 10.7 (17.9), 2048^2 36.5 (68.8), 4096^2 142 (239); FP64 1024^2 25.3
-// (33.6), 4096^2 356 (468); BF16 1024^2 10.9 (16.1), 4096^2 140 (178).
-// Sums over the wave of six values: halves, then 16-lane rows, of two values
-// are exchanged and added (each lane then carries one of them), then the rows
-// are added up.  Lane 0, 16, 32, 48 of `a`: values 0, 2, 1, 3; lane 0, 32 of
-// `b`: values 4, 5.
+// 1024^2 10.9 (17.9), 2048^2 34 (68.8), 4096^2 122 (239); FP64 1024^2 24
+// (33.6), 4096^2 310 (468); BF16 1024^2 10.9 (16.1), 4096^2 125 (178).
+// Sums over the wave of six values: halves, then 16-lane rows, then 8-lane
+// halves of rows, of two values are exchanged and added (each lane then
+// carries one of them), and the eight lanes that are left added up.  Lanes 0, 16, 32, 48
+// return values 0, 2, 1, 3, lanes 8 and 40 values 4 and 5.
 __device__ __forceinline__ double swap_add32(double x, double y)
 {
     const unsigned long long ux = __builtin_bit_cast(unsigned long long, x), uy = __builtin_bit_cast(unsigned long long, y);
@@ -822,28 +825,31 @@ __device__ __forceinline__ double swap_add16(double x, double y)
     return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
            __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
 }
-__device__ __forceinline__ double row_sum(double v)
+template <int CTRL> __device__ __forceinline__ double dpp_move(double v)
 {
-    v = dpp_add<0x128, 0xf>(v);      // row_ror:8
-    v = dpp_add<0x124, 0xf>(v);      // row_ror:4
-    v = dpp_add<0x122, 0xf>(v);      // row_ror:2
-    return dpp_add<0x121, 0xf>(v);   // row_ror:1
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
-__device__ __forceinline__ void wave_sums6(const double (&v)[6], double& a, double& b)
+__device__ __forceinline__ double wave_sums6(const double (&v)[6], bool upper8)
 {
     const double p = swap_add32(v[0], v[1]), q = swap_add32(v[2], v[3]), r = swap_add32(v[4], v[5]);
-    a = row_sum(swap_add16(p, q));
-    b = row_sum(swap_add16(r, r));
+    const double a = swap_add16(p, q), b = swap_add16(r, r);
+    double s = (upper8 ? b : a) + dpp_move<0x128>(upper8 ? a : b);      // row_ror:8
+    s += dpp_move<0x141>(s);                                            // row_half_mirror
+    s += dpp_move<0x4e>(s);                                             // quad_perm 2 3 0 1
+    return s + dpp_move<0xb1>(s);                                       // quad_perm 1 0 3 2
 }
 
-template <typename S, int K, bool NT>
+template <typename S, int K, int NR, bool NT>
 __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 ? 4 : 2))) void d2q9_band_kernel(
     D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
     typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
     int first, int nblocks, unsigned long long* __restrict__ faults)
 {
     static_assert(K == 1 || K == 3, "one or three steps");
-    using G = Band<K>;
+    using G = Band<K, NR>;
     using R = typename Store<S>::real;
     using raw = typename Store<S>::raw;
     constexpr int NW = G::NW, TX = G::TX, TY = G::TY, W0 = G::W0, C = G::kCells;
@@ -880,25 +886,23 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int i = 0; i < 9; ++i) d[i] = Store<S>::to_real(buf[i * C + cell - cy9(i) * W0 - cx9(i)]);
     };
-    // the two owned rows of this wave at one step, after their gather
-    auto owned = [&](int j, R (&d)[2][9], bool last) {
-        double v[6];
+    // the owned rows of this wave at one step, after their gather
+    const bool whole = X0 + TX <= nx && Y0 + TY <= ny;      // no cell outside the grid
+    auto owned = [&](int j, R (&d)[G::NR][9], bool last) {
+        R t[G::NR][6];                                  // the step's sums: mass, momentum, sensors
 #pragma unroll
-        for (int q = 0; q < 6; ++q) v[q] = 0.0;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int y = 2 * wave + r;
+        for (int r = 0; r < G::NR; ++r) {
+            const int y = G::NR * wave + r;
             const bool own = X0 + lane < nx && Y0 + y < ny;
             R drho, jx, jy;
             const CellSense<R> cs = cell_update<R, true, true>(d[r], rho0, inv_tau, drho, jx, jy);
-            // each cell's terms widen to FP64 before any add
-            v[0] += (double)(own ? drho : R(0));
-            v[1] += (double)(own ? jx : R(0));
-            v[2] += (double)(own ? jy : R(0));
-            v[3] += (double)(own ? cs.kl : R(0));
-            v[4] += (double)(own ? cs.neq : R(0));
-            v[5] += (double)(own ? cs.pi : R(0));
-            nfault += own && cs.fault ? 1u : 0u;
+            t[r][0] = drho;
+            t[r][1] = jx;
+            t[r][2] = jy;
+            t[r][3] = cs.kl;
+            t[r][4] = cs.neq;
+            t[r][5] = cs.pi;
+            nfault += (unsigned)__builtin_popcountll(__ballot(own && cs.fault));
             if (last && own) {
                 const unsigned X = (unsigned)(X0 + lane);
                 const long long prow = a.L.at(0, Y0 + y, 0), srow = (long long)(Y0 + y) * nx;
@@ -923,12 +927,28 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
                 }
             }
         }
-        double sa, sb;
-        wave_sums6(v, sa, sb);
-        if (lane % 16 == 0) {
-            const int row = lane / 16;              // rows 0 .. 3 of sa: values 0, 2, 1, 3
-            red[j][wave][row == 1 ? 2 : row == 2 ? 1 : row] = sa;
-            if (row % 2 == 0) red[j][wave][4 + row / 2] = sb;
+        if (j < first) return;                      // sums not kept
+        if (!whole) {
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) {
+                const bool own = X0 + lane < nx && Y0 + G::NR * wave + r < ny;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) t[r][q] = own ? t[r][q] : R(0);
+            }
+        }
+        // each cell's terms widen to FP64 before any add
+        double v[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            v[q] = (double)t[0][q];
+#pragma unroll
+            for (int r = 1; r < G::NR; ++r) v[q] += (double)t[r][q];
+        }
+        const double s = wave_sums6(v, lane & 8);
+        if (lane % 8 == 0) {
+            const int row = lane / 16;              // values 0, 2, 1, 3 by row; 4 and 5 in lanes 8 and 40
+            if (!(lane & 8)) red[j][wave][row == 1 ? 2 : row == 2 ? 1 : row] = s;
+            else if (row % 2 == 0) red[j][wave][4 + row / 2] = s;
         }
     };
     auto ring_update = [&](R (&d)[9]) {
@@ -937,12 +957,12 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
     };
 
     {   // ---- step 0: from global memory
-        R d[2][9];
+        R d[G::NR][9];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int r = 0; r < G::NR; ++r) {
             static_for<9>([&](auto ic) {
                 constexpr int i = decltype(ic)::value;
-                const int ys = G::wrap(Y0 + 2 * wave + r - cy9(i), ny);
+                const int ys = G::wrap(Y0 + G::NR * wave + r - cy9(i), ny);
                 d[r][i] = Store<S>::to_real((fin + a.L.at(i, ys, 0))[xs[1 - cx9(i)]]);
             });
         }
@@ -969,8 +989,8 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
         }
         owned(0, d, K == 1);
         if constexpr (K > 1) {
-            put(G::cell(lane, 2 * wave), d[0]);
-            put(G::cell(lane, 2 * wave + 1), d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) put(G::cell(lane, G::NR * wave + r), d[r]);
             if (ring) {
                 ring_update(g);
                 put(cell, g);
@@ -980,13 +1000,13 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
     __syncthreads();
     if constexpr (K > 1) {
         {   // ---- step 1: in place
-            R d[2][9], g[9];
+            R d[G::NR][9], g[9];
             int cell = 0;
             // the ring goes to the waves that had none, or less, of step 0's
             const int e = NW * kWave - 1 - (int)threadIdx.x;
             const bool ring = e < G::template ring<1>();
-            get(G::cell(lane, 2 * wave), d[0]);
-            get(G::cell(lane, 2 * wave + 1), d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) get(G::cell(lane, G::NR * wave + r), d[r]);
             owned(1, d, false);
             if (ring) {
                 int x, y;
@@ -996,15 +1016,15 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
                 ring_update(g);
             }
             __syncthreads();
-            put(G::cell(lane, 2 * wave), d[0]);
-            put(G::cell(lane, 2 * wave + 1), d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) put(G::cell(lane, G::NR * wave + r), d[r]);
             if (ring) put(cell, g);
         }
         __syncthreads();
         {   // ---- step 2: to global memory
-            R d[2][9];
-            get(G::cell(lane, 2 * wave), d[0]);
-            get(G::cell(lane, 2 * wave + 1), d[1]);
+            R d[G::NR][9];
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) get(G::cell(lane, G::NR * wave + r), d[r]);
             owned(2, d, true);
         }
         __syncthreads();
@@ -1018,7 +1038,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
         }
         if (j >= first) partials[((long long)(j - first) * nblocks + tile) * kNsums + k] = s;
     }
-    if (nfault) atomicAdd(faults, (unsigned long long)nfault);
+    if (nfault && lane == 0) atomicAdd(faults, (unsigned long long)nfault);      // counted per wave
 }
 
 // K steps of the state alone (no sensors, flags, sums or fault count), as the
@@ -1032,7 +1052,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
     typename Store<S>::raw* __restrict__ out1, typename Store<S>::raw* __restrict__ out2, int ntiles)
 {
     static_assert(K == 1 || K == 3, "one or three steps");
-    using G = Band<K>;
+    using G = Band<K, 2>;
     using R = typename Store<S>::real;
     using raw = typename Store<S>::raw;
     constexpr int W0 = G::W0, C = G::kCells;
@@ -1064,11 +1084,11 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
         R drho, jx, jy;
         (void)cell_update<R, false, true, false, true>(d, rho0, inv_tau, drho, jx, jy);
     };
-    auto store = [&](raw* out, const R (&d)[2][9]) {
+    auto store = [&](raw* out, const R (&d)[G::NR][9]) {
         if (!out || X0 + lane >= nx) return;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int Y = Y0 + 2 * wave + r;
+        for (int r = 0; r < G::NR; ++r) {
+            const int Y = Y0 + G::NR * wave + r;
             if (Y >= ny) break;
             const long long prow = a.L.at(0, Y, 0);
 #pragma unroll
@@ -1078,12 +1098,12 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
     };
 
     {   // ---- step 0: from global memory
-        R d[2][9], g[9];
+        R d[G::NR][9], g[9];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int r = 0; r < G::NR; ++r) {
             static_for<9>([&](auto ic) {
                 constexpr int i = decltype(ic)::value;
-                const int ys = G::wrap(Y0 + 2 * wave + r - cy9(i), ny);
+                const int ys = G::wrap(Y0 + G::NR * wave + r - cy9(i), ny);
                 d[r][i] = Store<S>::to_real((fin + a.L.at(i, ys, 0))[xs[1 - cx9(i)]]);
             });
         }
@@ -1106,12 +1126,12 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
                     g[i] = Store<S>::to_real(fin[i * a.L.pp + row[1 - cy9(i)] + col[1 - cx9(i)]]);
             }
         }
-        step(d[0]);
-        step(d[1]);
+#pragma unroll
+        for (int r = 0; r < G::NR; ++r) step(d[r]);
         store(out0, d);
         if constexpr (K > 1) {
-            put(G::cell(lane, 2 * wave), d[0]);
-            put(G::cell(lane, 2 * wave + 1), d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) put(G::cell(lane, G::NR * wave + r), d[r]);
             if (ring) {
                 step(g);
                 put(cell, g);
@@ -1121,15 +1141,15 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
     if constexpr (K > 1) {
         __syncthreads();
         {   // ---- step 1: in place
-            R d[2][9], g[9];
+            R d[G::NR][9], g[9];
             int cell = 0;
             // the ring goes to the waves that had none, or less, of step 0's
             const int e = G::NW * kWave - 1 - (int)threadIdx.x;
             const bool ring = e < G::template ring<1>();
-            get(G::cell(lane, 2 * wave), d[0]);
-            get(G::cell(lane, 2 * wave + 1), d[1]);
-            step(d[0]);
-            step(d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) get(G::cell(lane, G::NR * wave + r), d[r]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) step(d[r]);
             if (ring) {
                 int x, y;
                 G::template ring_cell<1>(e, x, y);
@@ -1139,17 +1159,17 @@ __global__ __launch_bounds__(kBandWaves * kWave) void d2q9_band_state_kernel(
             }
             store(out1, d);
             __syncthreads();
-            put(G::cell(lane, 2 * wave), d[0]);
-            put(G::cell(lane, 2 * wave + 1), d[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) put(G::cell(lane, G::NR * wave + r), d[r]);
             if (ring) put(cell, g);
         }
         __syncthreads();
         {   // ---- step 2: to global memory
-            R d[2][9];
-            get(G::cell(lane, 2 * wave), d[0]);
-            get(G::cell(lane, 2 * wave + 1), d[1]);
-            step(d[0]);
-            step(d[1]);
+            R d[G::NR][9];
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) get(G::cell(lane, G::NR * wave + r), d[r]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) step(d[r]);
             store(out2, d);
         }
     }
@@ -1397,15 +1417,15 @@ static hipError_t launch_tile_steps(const D2Q9Args& a, int k, const void* fin, v
     return hipGetLastError();
 }
 
-template <typename S>
+template <typename S, int NR>
 static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                                     uint8_t* flags, double* partials, int first, unsigned long long* faults,
                                     hipStream_t st)
 {
     using raw = typename Store<S>::raw;
     using R = typename Store<S>::real;
-    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
-    const int n = band_tiles(a.nx, a.ny);
+    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny, NR)) return hipErrorInvalidValue;
+    const int n = band_tiles(a.nx, a.ny, NR);
     const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
     // The non-temporal hint where rows are whole half lines only: partial
     // lines that leave the cache early are written twice (a step alone, plain /
@@ -1416,13 +1436,13 @@ static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, v
     raw* out = (raw*)fout;
     R* sv = (R*)sens;
     if (k == 3 && nt)
-        d2q9_band_kernel<S, 3, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 3, NR, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else if (k == 3)
-        d2q9_band_kernel<S, 3, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 3, NR, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else if (nt)
-        d2q9_band_kernel<S, 1, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 1, NR, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else
-        d2q9_band_kernel<S, 1, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+        d2q9_band_kernel<S, 1, NR, false><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     return hipGetLastError();
 }
 
@@ -1430,7 +1450,7 @@ template <typename S>
 static hipError_t launch_state(const D2Q9Args& a, int k, const void* fin, void* const* out, hipStream_t st)
 {
     using raw = typename Store<S>::raw;
-    const int n = band_tiles(a.nx, a.ny);
+    const int n = band_tiles(a.nx, a.ny, 2);
     const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
     if (k == 3)
         d2q9_band_state_kernel<S, 3><<<grid, block, 0, st>>>(a, (const raw*)fin, (raw*)out[0], (raw*)out[1],
@@ -1440,11 +1460,11 @@ static hipError_t launch_state(const D2Q9Args& a, int k, const void* fin, void* 
     return hipGetLastError();
 }
 
-bool d2q9_band_fits(int nx, int ny) { return band_fits(nx, ny); }
+bool d2q9_band_fits(int nx, int ny) { return band_fits(nx, ny, 2); }
 
 hipError_t launch_d2q9_state(int dtype, const D2Q9Args& a, int k, const void* fin, void* const* out, hipStream_t s)
 {
-    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
+    if ((k != 1 && k != 3) || !band_fits(a.nx, a.ny, 2)) return hipErrorInvalidValue;
     switch (dtype) {
     case 0: return launch_state<double>(a, k, fin, out, s);
     case 1: return launch_state<float>(a, k, fin, out, s);
@@ -1453,16 +1473,19 @@ hipError_t launch_d2q9_state(int dtype, const D2Q9Args& a, int k, const void* fi
 }
 
 // Tile forms (F(form, columns, rows, most steps)): the tile kernel's three,
-// then the band kernel.
+// then the band kernel with two and three rows a wave.
 #define LKS_TILE_FORMS(F) F(1, 8, 8, 7) F(2, 16, 16, 7) F(3, 32, 16, 5)
-constexpr int kBandForm = 4;
+constexpr int kBandForm = 4, kTallForm = 5;
 
 // The smallest tiles that one workgroup a CU can take (the fewest cells for
 // the ring's share of work: at FP32 128^2 8 x 8 tiles 1.9, 16 x 16 2.2 us a step;
 // at 256^2 16 x 16 2.6, 32 x 16 2.9, band 3.7; at 320^2 32 x 16 3.2, band 3.9; with
 // more tiles than CUs 16 x 16 takes 4.4 there), then the band kernel (384^2: 4.0
-// against 5.6), and on grids too narrow for it the largest tile that fits.
-// 32 x 16 tiles of FP64 cells do not fit the LDS.
+// against 5.6), and on grids too narrow for it the largest tile that fits.  The
+// band kernel takes three rows a wave (a smaller share of ring cells, but fewer
+// and longer workgroups) from eight tiles a CU on: FP32 us a step with two /
+// three rows 512^2 4.0 / 4.9, 1024^2 10.9 / 11.2, 2048^2 36.3 / 34.1, 4096^2 129.2 /
+// 122.3, FP64 4096^2 321 / 310, BF16 131 / 125.  32 x 16 tiles of FP64 cells do not fit the LDS.
 int d2q9_tile_of(int dtype, int nx, int ny)
 {
     constexpr long long kCUs = 256;
@@ -1472,7 +1495,8 @@ int d2q9_tile_of(int dtype, int nx, int ny)
         return V;
     LKS_TILE_FORMS(LKS_TILE_FITS)
 #undef LKS_TILE_FITS
-    if (band_fits(nx, ny)) return kBandForm;
+    if (band_fits(nx, ny, 3) && band_tiles(nx, ny, 3) >= 8 * kCUs) return kTallForm;
+    if (band_fits(nx, ny, 2)) return kBandForm;
     if (dtype != 0 && tile_fits(nx, 32, 5) && tile_fits(ny, 16, 5)) return 3;
     if (tile_fits(nx, 16, 7) && tile_fits(ny, 16, 7)) return 2;
     return tile_fits(nx, 8, 7) && tile_fits(ny, 8, 7) ? 1 : 0;
@@ -1484,7 +1508,8 @@ int d2q9_tile_steps(int tile)
 #define LKS_TILE_STEPS(V, TX, TY, K) case V: return K;
     LKS_TILE_FORMS(LKS_TILE_STEPS)
 #undef LKS_TILE_STEPS
-    case kBandForm: return kBandK;
+    case kBandForm:
+    case kTallForm: return kBandK;
     default: return 0;
     }
 }
@@ -1495,14 +1520,15 @@ int d2q9_tile_blocks(int tile, int nx, int ny)
 #define LKS_TILE_BLOCKS(V, TX, TY, K) case V: return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
     LKS_TILE_FORMS(LKS_TILE_BLOCKS)
 #undef LKS_TILE_BLOCKS
-    case kBandForm: return band_tiles(nx, ny);
+    case kBandForm: return band_tiles(nx, ny, 2);
+    case kTallForm: return band_tiles(nx, ny, 3);
     default: return 0;
     }
 }
 
 bool d2q9_tile_single(int dtype, int tile, bool nt, bool rows, bool wide)
 {
-    return tile != kBandForm || dtype > 1 || !nt || !rows || !wide;
+    return (tile != kBandForm && tile != kTallForm) || dtype > 1 || !nt || !rows || !wide;
 }
 
 template <typename S>
@@ -1517,7 +1543,8 @@ static hipError_t launch_tile_form(const D2Q9Args& a, int k, const void* fin, vo
         if constexpr (sizeof(typename Store<S>::raw) <= 4)
             return launch_tile_steps<S, 32, 16, 5>(a, k, fin, fout, sens, flags, partials, first, faults, st);
         return hipErrorInvalidValue;
-    case kBandForm: return launch_band_steps<S>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+    case kBandForm: return launch_band_steps<S, 2>(a, k, fin, fout, sens, flags, partials, first, faults, st);
+    case kTallForm: return launch_band_steps<S, 3>(a, k, fin, fout, sens, flags, partials, first, faults, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) void adj_band_kernel(D2Q9Args a
                                                                      const R* __restrict__ lam_in,
                                                                      R* __restrict__ lam_out, int ntiles)
 {
-    using G = Band<K>;
+    using G = Band<K, 2>;
     constexpr int W0 = G::W0, C = G::kCells;
     __shared__ R buf[9 * C];
     const int tile = G::tile();
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kBandWaves * kWave) void adj_band_kernel(D2Q9Args a
         constexpr int SIGN = decltype(sc)::value;
         sfor<9>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            const int ys = G::wrap(Y0 + 2 * wave + r - SIGN * acy(i), ny);
+            const int ys = G::wrap(Y0 + G::NR * wave + r - SIGN * acy(i), ny);
             v[i] = (f + a.L.at(i, ys, 0))[xs[1 - SIGN * acx(i)]];
         });
     };
@@ -226,14 +226,14 @@ __global__ __launch_bounds__(kBandWaves * kWave) void adj_band_kernel(D2Q9Args a
         // the first step's ring goes to the low threads, the next one's to the high
         const int e = first ? (int)threadIdx.x : G::NW * kWave - 1 - (int)threadIdx.x;
         const bool ring = e < G::template ring<H>();
-        R out[2][9], og[9];
+        R out[G::NR][9], og[9];
         int cell = 0;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int r = 0; r < G::NR; ++r) {
             R d[9], l[9];
             pull_row(fwd, f, r, d);
             if constexpr (first) pull_row(bwd, lam_in, r, l);
-            else get(G::cell(lane, 2 * wave + r), l);
+            else get(G::cell(lane, G::NR * wave + r), l);
             collide_adjoint(d, l, rho0, tau, out[r]);
         }
         if constexpr (!last) {
@@ -248,14 +248,14 @@ __global__ __launch_bounds__(kBandWaves * kWave) void adj_band_kernel(D2Q9Args a
                 collide_adjoint(d, l, rho0, tau, og);
             }
             if constexpr (!first) __syncthreads();
-            put(G::cell(lane, 2 * wave), out[0]);
-            put(G::cell(lane, 2 * wave + 1), out[1]);
+#pragma unroll
+            for (int r = 0; r < G::NR; ++r) put(G::cell(lane, G::NR * wave + r), out[r]);
             if (ring) put(cell, og);
             __syncthreads();
         } else if (X0 + lane < nx) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int Y = Y0 + 2 * wave + r;
+            for (int r = 0; r < G::NR; ++r) {
+                const int Y = Y0 + G::NR * wave + r;
                 if (Y >= ny) break;
                 const long long prow = a.L.at(0, Y, 0);
 #pragma unroll
@@ -332,7 +332,7 @@ template <typename R>
 static hipError_t launch_adj_band(const D2Q9Args& a, int k, const void* const* f, const void* lam_in, void* lam_out,
                                   hipStream_t s)
 {
-    const int n = band_tiles(a.nx, a.ny);
+    const int n = band_tiles(a.nx, a.ny, 2);
     const dim3 grid((unsigned)((n + 63) / 64 * 64)), block(kBandWaves * kWave);
     if (k == 3)
         adj_band_kernel<R, 3><<<grid, block, 0, s>>>(a, R(a.rho0), R(a.tau), (const R*)f[0], (const R*)f[1],
@@ -346,7 +346,7 @@ static hipError_t launch_adj_band(const D2Q9Args& a, int k, const void* const* f
 hipError_t launch_adj_steps(int dtype, const D2Q9Args& a, int k, const void* const* pop_prev, const void* lam_in,
                             void* lam_out, hipStream_t s)
 {
-    if ((k != 2 && k != 3) || !band_fits(a.nx, a.ny)) return hipErrorInvalidValue;
+    if ((k != 2 && k != 3) || !band_fits(a.nx, a.ny, 2)) return hipErrorInvalidValue;
     if (dtype == 0) return launch_adj_band<double>(a, k, pop_prev, lam_in, lam_out, s);
     if (dtype == 1) return launch_adj_band<float>(a, k, pop_prev, lam_in, lam_out, s);
     return hipErrorInvalidValue;

@@ -11,17 +11,22 @@ namespace lks {
 // at most one period beyond it on either side (what the kernels wrap).
 constexpr bool tile_fits(int n, int T, int K) { return n >= K && (n - 1) / T * T + T + K <= 2 * n; }
 
-// K steps of a tile of 64 columns and 2 NW rows: two rows a wave, one lane a
-// column.  Cells of the tile and a ring of H0 = K - 1 cells lie in LDS at
-// (y + H0) W0 + x + H0, x and y relative to the tile.
+// K steps of a tile of 64 columns: eight waves (two a SIMD: six and twelve
+// measured 30 % slower) of NR rows each, one lane a column.  Cells of the tile
+// and a ring of H0 = K - 1 cells lie in LDS at (y + H0) W0 + x + H0, x and y
+// relative to the tile.
 constexpr int kBandWaves = 8;
-constexpr int kBandX = kWave, kBandY = 2 * kBandWaves, kBandK = 3;
-constexpr bool band_fits(int nx, int ny) { return tile_fits(nx, kBandX, kBandK) && tile_fits(ny, kBandY, kBandK); }
-inline int band_tiles(int nx, int ny) { return ((nx + kBandX - 1) / kBandX) * ((ny + kBandY - 1) / kBandY); }
+constexpr int kBandX = kWave, kBandK = 3;
+constexpr int band_y(int nr) { return nr * kBandWaves; }
+constexpr bool band_fits(int nx, int ny, int nr) { return tile_fits(nx, kBandX, kBandK) && tile_fits(ny, band_y(nr), kBandK); }
+constexpr int band_tiles(int nx, int ny, int nr)
+{
+    return ((nx + kBandX - 1) / kBandX) * ((ny + band_y(nr) - 1) / band_y(nr));
+}
 
-template <int K> struct Band {
+template <int K, int NR_> struct Band {
     static_assert(K >= 1 && K <= kBandK, "one to three steps");
-    static constexpr int NW = kBandWaves, TX = kBandX, TY = kBandY, H0 = K - 1, W0 = TX + 2 * H0;
+    static constexpr int NW = kBandWaves, NR = NR_, TX = kBandX, TY = band_y(NR), H0 = K - 1, W0 = TX + 2 * H0;
     static constexpr int kCells = K == 1 ? 1 : W0 * (TY + 2 * H0);
     // cells of the ring of H cells: one a thread at most
     template <int H> static constexpr int ring() { return (TX + 2 * H) * (TY + 2 * H) - TX * TY; }

@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
 THR = np.array([[1e-6, 1e-5], [1e-3, 3e-3], [1e-3, 2e-3], [np.inf, np.inf]])
 GRIDS = [(7, 9), (8, 8), (9, 12), (12, 12), (16, 15), (20, 37), (37, 22), (66, 18), (129, 128), (257, 255),
          (300, 291), (301, 40), (40, 301), (34, 4100), (33, 4100), (65, 2100), (66, 2100), (4200, 10), (4200, 9),
-         (4200, 17), (4200, 18), (19, 4000), (563, 517), (520, 1031)]
+         (4200, 17), (4200, 18), (19, 4000), (563, 517), (520, 1031), (131100, 20)]
 
 
 def _pair(nx, ny, dtype, layout, max_steps, far=False, **kw):
