@@ -183,7 +183,7 @@ lks::D2Q25Args d2q25_args(const lks_config& c)
     a.aux = nullptr;
     a.nt_stores = 0;
     a.quiet = 0;
-    lks::d2q25_tile_shape(c.dtype, c.model, &a.tile_x, &a.tile_y);
+    lks::d2q25_tile_shape(c.dtype, c.model, c.nx, c.ny, &a.tile_x, &a.tile_y);
     a.tiles_x = (c.nx + a.tile_x - 1) / a.tile_x;
     a.tiles_y = (c.ny + a.tile_y - 1) / a.tile_y;
     a.nblocks = a.tiles_x * a.tiles_y;

@@ -132,8 +132,8 @@ bool d2q9_tile_single(int dtype, int tile, bool nt, bool rows, bool wide);
 hipError_t launch_d2q25(int dtype, const D2Q25Args& a, const void* fin, void* fout, void* sens,
                         uint8_t* flags, double* partials, unsigned long long* faults,
                         hipStream_t s);
-// workgroup tile (cells) of the D2Q25 kernel for a storage type and model
-void d2q25_tile_shape(int dtype, int model, int* tx, int* ty);
+// workgroup tile (cells) of the D2Q25 kernel for a storage type, model and grid
+void d2q25_tile_shape(int dtype, int model, int nx, int ny, int* tx, int* ty);
 
 // equilibrium initial states from FP64 fields [ny][nx] (n = nx*ny cells)
 hipError_t launch_d2q9_init(int dtype, long long n, const PopLayout& L, double rho0, const double* rho,
