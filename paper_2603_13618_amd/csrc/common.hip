@@ -24,27 +24,37 @@ __global__ __launch_bounds__(kBlock) void chunk_sums_kernel(double* __restrict__
     if (threadIdx.x < kNsums) p[(long long)blockIdx.x * kBlock * kNsums + threadIdx.x] = out[threadIdx.x];
 }
 
-// One workgroup per step over n partials `stride` workgroups apart: thread t
-// adds partials t, t + 256, ... in order, then the fixed wave/LDS tree.
-__global__ __launch_bounds__(kBlock) void finalize_kernel(const double* __restrict__ partials, int nblocks,
-                                                     int n, int stride, double* __restrict__ sums,
-                                                     long long row0, int max_rows, double mass_ref,
-                                                     double energy_ref)
+// One workgroup of NT threads per step over n partials `stride` workgroups
+// apart: thread t adds partials t, t + NT, ... in order, then the fixed
+// wave/LDS tree.
+template <int NT>
+__global__ __launch_bounds__(NT) void finalize_kernel(const double* __restrict__ partials, int nblocks,
+                                                 int n, int stride, double* __restrict__ sums,
+                                                 long long row0, int max_rows, double mass_ref,
+                                                 double energy_ref)
 {
+    constexpr int NW = NT / kWave;
+    __shared__ double red[NW][kNsums];
     const int step = blockIdx.x;
     const double* p = partials + (long long)step * nblocks * kNsums;
     double acc[kNsums];
 #pragma unroll
     for (int k = 0; k < kNsums; ++k) acc[k] = 0.0;
-    for (int b = threadIdx.x; b < n; b += kBlock) {
+    for (int b = threadIdx.x; b < n; b += NT) {
 #pragma unroll
         for (int k = 0; k < kNsums; ++k) acc[k] += p[(long long)b * stride * kNsums + k];
     }
-    __shared__ double out[kNsums];
-    block_sums(acc, out);
+#pragma unroll
+    for (int k = 0; k < kNsums; ++k) acc[k] = wave_sum(acc[k]);
+    if (threadIdx.x % kWave == 0) {
+#pragma unroll
+        for (int k = 0; k < kNsums; ++k) red[threadIdx.x / kWave][k] = acc[k];
+    }
     __syncthreads();
     if (threadIdx.x < kNsums) {
-        double v = out[threadIdx.x];
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[w][threadIdx.x];
         if (threadIdx.x == 0) v += mass_ref;
         if (threadIdx.x == 3) v += energy_ref;
         const long long row = (row0 + step) % max_rows;
@@ -52,22 +62,31 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const double* __restri
     }
 }
 
+// Up to this many workgroups one workgroup of 1024 threads a step reads all the
+// partials: four each at most, and one launch less (a step alone, BF16 1024^2:
+// 22.8 -> 20.7 us; 2048 x 1024 32.3 -> 30.5; no gain from 8192 on).  Far above, one
+// workgroup would walk the partials alone (32,768: 77 us per batch of 8 steps).
+constexpr int kFinalizeOne = 4096;
+
 hipError_t launch_finalize(double* partials, int nblocks, int nsteps, double* sums, long long row0,
                            int max_rows, double mass_ref, double energy_ref, hipStream_t s)
 {
     if (nsteps <= 0) return hipSuccess;
+    if (nblocks <= kBlock) {
+        finalize_kernel<kBlock><<<dim3(nsteps), dim3(kBlock), 0, s>>>(partials, nblocks, nblocks, 1, sums, row0,
+                                                                      max_rows, mass_ref, energy_ref);
+        return hipGetLastError();
+    }
     int n = nblocks, stride = 1;
-    if (nblocks > kBlock) {
-        // a single workgroup per step would walk all the partials alone
-        // (77 us per batch of 8 steps on 32,768 workgroups)
+    if (nblocks > kFinalizeOne) {
         n = (nblocks + kBlock - 1) / kBlock;
         stride = kBlock;
         chunk_sums_kernel<<<dim3((unsigned)n, (unsigned)nsteps), dim3(kBlock), 0, s>>>(partials, nblocks);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    finalize_kernel<<<dim3(nsteps), dim3(kBlock), 0, s>>>(partials, nblocks, n, stride, sums, row0, max_rows,
-                                                          mass_ref, energy_ref);
+    finalize_kernel<1024><<<dim3(nsteps), dim3(1024), 0, s>>>(partials, nblocks, n, stride, sums, row0, max_rows,
+                                                              mass_ref, energy_ref);
     return hipGetLastError();
 }
 
