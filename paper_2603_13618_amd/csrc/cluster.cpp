@@ -17,9 +17,9 @@
 // admissible cut is accepted as it is.  The low part of a cut is clustered
 // first, so the output order is depth-first.
 //
-// Signatures of a box are read from two prefix-sum tables (row-wise and
-// column-wise cumulative tile counts), so each costs O(box side), not
-// O(box area).
+// Signatures of a box are differences of two rows of prefix-sum tables (counts
+// summed over the tile rows below and over the tile columns to the left), so
+// each costs O(box side), not O(box area), and reads memory in order.
 #include <cstdint>
 #include <cstdlib>
 #include <vector>
@@ -30,19 +30,9 @@ namespace {
 
 struct Grid {
     int tx, ty, ts, nx, ny;
-    std::vector<int64_t> rowcum;   // rowcum[j][i]: sum of counts[j][0 .. i-1], width tx+1
-    std::vector<int64_t> colcum;   // colcum[i][j]: sum of counts[0 .. j-1][i], width ty+1
+    std::vector<int64_t> below;    // below[j][i]: sum of counts[0 .. j-1][i], ty+1 rows of tx
+    std::vector<int64_t> left;     // left[i][j]: sum of counts[j][0 .. i-1], tx+1 rows of ty
 
-    int64_t row_sum(int j, int i0, int i1) const
-    {
-        const int64_t* r = &rowcum[(size_t)j * (tx + 1)];
-        return r[i1] - r[i0];
-    }
-    int64_t col_sum(int i, int j0, int j1) const
-    {
-        const int64_t* c = &colcum[(size_t)i * (ty + 1)];
-        return c[j1] - c[j0];
-    }
     int64_t cells(int lo, int hi, int n) const
     {
         const int64_t end = (int64_t)hi * ts < n ? (int64_t)hi * ts : n;
@@ -61,57 +51,72 @@ void signatures(const Grid& g, int i0, int j0, int i1, int j1, std::vector<int64
 {
     sx.resize(i1 - i0);
     sy.resize(j1 - j0);
-    for (int i = i0; i < i1; ++i) sx[i - i0] = g.col_sum(i, j0, j1);
-    for (int j = j0; j < j1; ++j) sy[j - j0] = g.row_sum(j, i0, i1);
+    const int64_t* b0 = &g.below[(size_t)j0 * g.tx + i0];
+    const int64_t* b1 = &g.below[(size_t)j1 * g.tx + i0];
+    for (int i = 0; i < i1 - i0; ++i) sx[i] = b1[i] - b0[i];
+    const int64_t* l0 = &g.left[(size_t)i0 * g.ty + j0];
+    const int64_t* l1 = &g.left[(size_t)i1 * g.ty + j0];
+    for (int j = 0; j < j1 - j0; ++j) sy[j] = l1[j] - l0[j];
 }
 
-Cut find_cut(const std::vector<int64_t>& sx, const std::vector<int64_t>& sy, int min_tiles)
+struct Signature {
+    const int64_t* s;
+    int n;
+};
+
+Cut find_cut(const Signature& sx, const Signature& sy, int min_tiles)
 {
-    const std::vector<int64_t>* sig[2] = {&sx, &sy};
+    const Signature* sig[2] = {&sx, &sy};
     Cut best;
-    long long bkey0 = 0, bkey1 = 0, bkey2 = 0;
-    // 1. holes
+    // 1. holes: outwards from the middle of each axis, the lower index of a
+    // pair first, so the first hole found is the axis's nearest
+    int bdist = 0;
     for (int axis = 0; axis < 2; ++axis) {
-        const std::vector<int64_t>& s = *sig[axis];
-        const int n = (int)s.size();
-        for (int k = 0; k < n; ++k) {
-            if (s[k] != 0 || k < min_tiles || n - k < min_tiles) continue;
-            const long long key = std::llabs(2LL * k + 1 - n);
-            // lexicographic (distance, axis, k); axes and k are visited in order
-            if (!best.found || key < bkey0) {
-                best.found = true;
-                best.axis = axis;
-                best.k = k;
-                bkey0 = key;
-            }
+        const int64_t* s = sig[axis]->s;
+        const int n = sig[axis]->n;
+        for (int dist = (n + 1) % 2; dist < n; dist += 2) {     // |2k + 1 - n|
+            if (best.found && dist >= bdist) break;
+            const int lo = (n - 1 - dist) / 2, hi = (n - 1 + dist) / 2;
+            const int k = lo >= min_tiles && n - lo >= min_tiles && s[lo] == 0   ? lo
+                          : hi >= min_tiles && n - hi >= min_tiles && s[hi] == 0 ? hi
+                                                                                  : -1;
+            if (k < 0) continue;
+            best.found = true;
+            best.axis = axis;
+            best.k = k;
+            bdist = dist;
+            break;
         }
     }
     if (best.found) return best;
     // 2. inflections
+    int64_t bjump = 0;
+    int bmid = 0;
     for (int axis = 0; axis < 2; ++axis) {
-        const std::vector<int64_t>& s = *sig[axis];
-        const int n = (int)s.size();
+        const int64_t* s = sig[axis]->s;
+        const int n = sig[axis]->n;
         if (n < 4) continue;
-        for (int k = 2; k <= n - 2; ++k) {
-            if (k < min_tiles || n - k < min_tiles) continue;
-            const long long lap_a = s[k] - 2 * s[k - 1] + s[k - 2];    // at tile k - 1
-            const long long lap_b = s[k + 1] - 2 * s[k] + s[k - 1];    // at tile k
-            if (!((lap_a < 0 && lap_b > 0) || (lap_a > 0 && lap_b < 0))) continue;
-            const long long jump = std::llabs(lap_b - lap_a);
-            const long long mid = std::llabs(2LL * k - n);
-            const bool better = !best.found || jump > bkey1 || (jump == bkey1 && mid < bkey2);
-            if (better) {
-                best.found = true;
-                best.axis = axis;
-                best.k = k;
-                bkey1 = jump;
-                bkey2 = mid;
-            }
+        const int k0 = min_tiles > 2 ? min_tiles : 2, k1 = n - (min_tiles > 2 ? min_tiles : 2);
+        if (k0 > k1) continue;
+        int64_t lap_a = s[k0] - 2 * s[k0 - 1] + s[k0 - 2];             // at tile k - 1
+        for (int k = k0; k <= k1; ++k) {
+            const int64_t lap_b = s[k + 1] - 2 * s[k] + s[k - 1];      // at tile k
+            const int64_t jump = lap_b > lap_a ? lap_b - lap_a : lap_a - lap_b;
+            const bool cross = (lap_a < 0 && lap_b > 0) || (lap_a > 0 && lap_b < 0);
+            lap_a = lap_b;
+            if (!cross || (best.found && jump < bjump)) continue;
+            const int mid = std::abs(2 * k - n);
+            if (best.found && jump == bjump && mid >= bmid) continue;
+            best.found = true;
+            best.axis = axis;
+            best.k = k;
+            bjump = jump;
+            bmid = mid;
         }
     }
     if (best.found) return best;
     // 3. bisection of the longer axis
-    const int nx = (int)sx.size(), ny = (int)sy.size();
+    const int nx = sx.n, ny = sy.n;
     const int axis = nx >= ny ? 0 : 1;
     const int n = axis == 0 ? nx : ny;
     if (n / 2 >= min_tiles && n - n / 2 >= min_tiles) {
@@ -140,15 +145,23 @@ extern "C" lks_status lks_cluster(const int32_t* counts, int32_t nx, int32_t ny,
     g.ny = ny;
     g.tx = (nx + ts - 1) / ts;
     g.ty = (ny + ts - 1) / ts;
-    g.rowcum.assign((size_t)g.ty * (g.tx + 1), 0);
-    g.colcum.assign((size_t)g.tx * (g.ty + 1), 0);
-    for (int j = 0; j < g.ty; ++j)
+    g.below.resize((size_t)(g.ty + 1) * g.tx);
+    g.left.resize((size_t)(g.tx + 1) * g.ty);
+    for (int i = 0; i < g.tx; ++i) g.below[i] = 0;
+    for (int j = 0; j < g.ty; ++j) {
+        const int32_t* c = &counts[(size_t)j * g.tx];
+        const int64_t* from = &g.below[(size_t)j * g.tx];
+        int64_t* to = &g.below[(size_t)(j + 1) * g.tx];
+        int32_t bad = 0;
         for (int i = 0; i < g.tx; ++i) {
-            const int64_t c = counts[(size_t)j * g.tx + i];
-            if (c < 0) return LKS_EINVAL;
-            g.rowcum[(size_t)j * (g.tx + 1) + i + 1] = g.rowcum[(size_t)j * (g.tx + 1) + i] + c;
-            g.colcum[(size_t)i * (g.ty + 1) + j + 1] = g.colcum[(size_t)i * (g.ty + 1) + j] + c;
+            bad |= c[i];
+            to[i] = from[i] + c[i];
         }
+        if (bad < 0) return LKS_EINVAL;             // some count is negative
+        int64_t sum = 0;
+        g.left[j] = 0;
+        for (int i = 0; i < g.tx; ++i) g.left[(size_t)(i + 1) * g.ty + j] = sum += c[i];
+    }
 
     int32_t n = 0;
     std::vector<Work> stack;          // depth-first, low part of every cut first
@@ -167,12 +180,14 @@ extern "C" lks_status lks_cluster(const int32_t* counts, int32_t nx, int32_t ny,
         while (sy[c] == 0) ++c;
         while (sy[d] == 0) --d;
         const int i0 = w.i0 + a, i1 = w.i0 + b + 1, j0 = w.j0 + c, j1 = w.j0 + d + 1;
-        signatures(g, i0, j0, i1, j1, sx, sy);
+        // its own signatures: no tag lies in the tiles cut off, so the others'
+        // values stand
+        const Signature bx = {sx.data() + a, b - a + 1}, by = {sy.data() + c, d - c + 1};
         int64_t tagged = 0;
-        for (int64_t v : sx) tagged += v;
+        for (int i = 0; i < bx.n; ++i) tagged += bx.s[i];
         const int64_t area = g.cells(i0, i1, nx) * g.cells(j0, j1, ny);
         Cut cut;
-        if (!((double)tagged >= eff * (double)area)) cut = find_cut(sx, sy, min_tiles);
+        if (!((double)tagged >= eff * (double)area)) cut = find_cut(bx, by, min_tiles);
         if (!cut.found) {
             if (n < max_boxes) {
                 lks_box& o = boxes[n];

@@ -428,14 +428,15 @@ def cluster(counts, nx, ny, ts, eff=0.98, min_tiles=1, max_boxes=None):
     c = np.ascontiguousarray(counts, dtype=np.int32)
     if max_boxes is None:
         max_boxes = max(int(np.count_nonzero(c)), 1)       # at most one box per tagged tile
-    boxes = (Box * max_boxes)()
+    boxes = np.empty((max_boxes, 4), np.int32)              # lks_box records
     n = ctypes.c_int32()
     st = lib().lks_cluster(c.ctypes.data_as(ctypes.c_void_p), int(nx), int(ny), int(ts), float(eff),
-                           int(min_tiles), boxes, int(max_boxes), ctypes.byref(n))
+                           int(min_tiles), boxes.ctypes.data_as(ctypes.POINTER(Box)), int(max_boxes),
+                           ctypes.byref(n))
     if st != 0:
         raise LksError(st, f"lks_cluster needs {n.value} boxes (room for {max_boxes})"
                        if n.value > max_boxes else "invalid clustering arguments")
-    return [(b.x0, b.y0, b.x1, b.y1) for b in boxes[: n.value]]
+    return list(zip(*boxes[: n.value].T.tolist()))
 
 
 NOALLOC_SCRATCH_BYTES = 16 << 20      # LKS_NOALLOC_SCRATCH_BYTES
