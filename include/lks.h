@@ -205,7 +205,7 @@ typedef struct {
                              buffers exceed the 256 MB last-level cache),
                              1 plain, 2 non-temporal (a launch hint only:
                              results are identical).  D2Q9 every storage
-                             type; D2Q25 FP32 on grids of whole tiles      */
+                             type; D2Q25 FP32 on rows of a multiple of 16  */
     int32_t launch_steps; /* fused D2Q9 steps per launch: 0 picks (several steps
                              of a tile per launch where a call has them, with
                              automatic launch_rows, launch_vec and launch_nt;

@@ -388,37 +388,42 @@ __device__ __forceinline__ R advect(R o, const AdvScale<R>& sc, const R* t, cons
 
 // Workgroup -> tile.  Consecutive workgroup ids go to the eight XCDs in turn
 // (id mod 8), each with its own L2, so the order decides which halo rows and
-// columns a tile finds in its XCD's L2.  LKS_Q25_XCD_MAP 1 (default): XCD k
-// sweeps row band k of the tile rows row by row, so the halo columns always
-// come from its own L2 and only the band's first and last tile rows read
-// halo rows another XCD loaded; 0: XCD k sweeps column band k of the tile
-// columns row by row (every band edge reads its halo columns from another
-// XCD's band); 2: plain row-major order.  Measured at 2048^2 (FP32 kernel
-// time per step, a 3-wave build of the single-distribution kernel): single
-// distribution 354 / 376 / 362 us for maps 1 / 0 / 2, double distribution
-// 799 / 808 / 877 us.  Bands swept column by column were worse (read bytes
-// per step 913 and 1422 MB against 614 MB, 282 and 329 us against 277 us):
-// the x-halo of a 32-wide tile is two floats of each neighbour's 128-byte
-// rows, so horizontal neighbours must run close together in time.  Shapes
-// that do not divide into 8 bands use row-major order.
-#ifndef LKS_Q25_XCD_MAP
-#define LKS_Q25_XCD_MAP 1
-#endif
-__device__ __forceinline__ void xcd_tile(const D2Q25Args& a, int& tile_x, int& tile_y)
+// columns a tile finds in its XCD's L2: XCD k sweeps the k-th eighth of the
+// tiles in row-major order, so that the halo columns almost always come from
+// its own L2 and the halo rows do but for its first and last tile row.
+// Measured at 2048^2 (FP32 kernel time per step, a 3-wave build of the
+// single-distribution kernel): 354 us against 376 with each XCD sweeping a band
+// of tile columns and 362 in plain row-major order; double distribution 799 /
+// 808 / 877 us.  Bands swept column by column were worse (read bytes per step
+// 913 and 1422 MB against 614 MB, 282 and 329 us against 277 us): the x-halo of
+// a 32-wide tile is two floats of each neighbour's 128-byte rows, so horizontal
+// neighbours must run close together in time.  Returns the tile's index, or -1
+// for the workgroups that round the grid up to eight equal shares.
+__device__ __forceinline__ int xcd_tile(const D2Q25Args& a, int& tile_x, int& tile_y)
 {
-    const int b = blockIdx.x;
-    if (LKS_Q25_XCD_MAP == 0 && a.tiles_x % 8 == 0) {
-        const int bw = a.tiles_x / 8, l = b / 8;
-        tile_x = (b % 8) * bw + l % bw;
-        tile_y = l / bw;
-    } else if (LKS_Q25_XCD_MAP == 1 && a.tiles_y % 8 == 0) {
-        const int bh = a.tiles_y / 8, l = b / 8;
-        tile_x = l % a.tiles_x;
-        tile_y = (b % 8) * bh + l / a.tiles_x;
-    } else {
-        tile_x = b % a.tiles_x;
-        tile_y = b / a.tiles_x;
-    }
+    const long long n = (long long)a.tiles_x * a.tiles_y;
+    const int k = blockIdx.x % 8;
+    const int t = (int)(k * n / 8) + blockIdx.x / 8;
+    if (t >= (int)((k + 1) * n / 8)) return -1;
+    tile_x = t % a.tiles_x;
+    tile_y = t / a.tiles_x;
+    return t;
+}
+static unsigned xcd_grid(const D2Q25Args& a) { return (unsigned)((a.nblocks + 7) / 8 * 8); }
+
+// First cell of tile i of T along an axis of n cells.  A last tile that would
+// reach over the edge is moved back inside (EDGE = false): the cells that it
+// shares with its neighbour are computed twice, to the same bits, and counted
+// in the sums by their first tile alone.  So any grid of at least one tile runs
+// the form in which every thread owns a cell, and no store needs a branch
+// around it (a branch per store cuts the arithmetic of a velocity group into
+// separate scheduling regions).  us per step with the branches, and tiles in
+// row-major order where their rows do not divide by eight / now: double
+// distribution FP32 1000^2 232 / 177, 500 x 301 57 / 42, FP64 500 x 301 115 / 83;
+// single distribution FP32 2001 x 1501 235 / 215, 500 x 301 23.6 / 19.4.
+template <bool EDGE> __device__ __forceinline__ int tile_origin(int i, int T, int n)
+{
+    return EDGE ? i * T : min(i * T, n - T);
 }
 
 template <int TX, int TY> struct Tile {
@@ -556,13 +561,13 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(Q25Wave
     const int nx = a.nx, ny = a.ny;
     const long long plane = a.plane;
     int tile_x, tile_y;
-    xcd_tile(a, tile_x, tile_y);
+    const int tile = xcd_tile(a, tile_x, tile_y);
+    if (tile < 0) return;                       // whole workgroups
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-    const int X0 = tile_x * TX, Y0 = tile_y * TY;
+    const int X0 = tile_origin<EDGE>(tile_x, TX, nx), Y0 = tile_origin<EDGE>(tile_y, TY, ny);
     const int X = X0 + tx, Y = Y0 + ty;
-    // EDGE = false: the grid is a whole number of tiles, every thread owns a
-    // cell, and no store needs a branch around it (a branch per store cuts
-    // the arithmetic of a velocity group into separate scheduling regions)
+    // EDGE = false: at least one tile along either axis, every thread owns a
+    // cell (tile_origin)
     const bool active = !EDGE || (X < nx && Y < ny);
     const int gxc = ghost_index(X, nx, a.bc_x), gyc = ghost_index(Y, ny, a.bc_y);
     constexpr int HR = (4 * TX + NT - 1) / NT;
@@ -764,17 +769,19 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(Q25Wave
             sens[3 * plane + off] = s_q;
             flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
         }
-        if (fault) atomicAdd(faults, 1ull);
-        acc[0] = (double)drho;
-        acc[1] = (double)jx;
-        acc[2] = (double)jy;
-        acc[3] = (double)edev;
-        acc[4] = (double)s_kl;
-        acc[5] = (double)neq;
-        acc[6] = (double)s_pi;
-        acc[7] = (double)s_q;
+        if (X >= tile_x * TX && Y >= tile_y * TY) {     // not counted by the tile before
+            if (fault) atomicAdd(faults, 1ull);
+            acc[0] = (double)drho;
+            acc[1] = (double)jx;
+            acc[2] = (double)jy;
+            acc[3] = (double)edev;
+            acc[4] = (double)s_kl;
+            acc[5] = (double)neq;
+            acc[6] = (double)s_pi;
+            acc[7] = (double)s_q;
+        }
     }
-    block_sums_n<NT / kWave>(acc, partials + (long long)blockIdx.x * kNsums);
+    block_sums_n<NT / kWave>(acc, partials + (long long)tile * kNsums);
 }
 
 // ---------------------------------------------------------------------------
@@ -824,9 +831,10 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
     const int nx = a.nx, ny = a.ny;
     const long long plane = a.plane;
     int tile_x, tile_y;
-    xcd_tile(a, tile_x, tile_y);
+    const int tile = xcd_tile(a, tile_x, tile_y);
+    if (tile < 0) return;                       // whole workgroups
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-    const int X0 = tile_x * TX, Y0 = tile_y * TY;
+    const int X0 = tile_origin<EDGE>(tile_x, TX, nx), Y0 = tile_origin<EDGE>(tile_y, TY, ny);
     const int X = X0 + tx, Y = Y0 + ty;
     const bool active = !EDGE || (X < nx && Y < ny);     // EDGE: as in d2q25_kernel
     const int gxc = ghost_index(X, nx, a.bc_x), gyc = ghost_index(Y, ny, a.bc_y);
@@ -1171,17 +1179,19 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
             for (int s = 0; s < 5; ++s) sens[s * plane + off] = sv[s];
             flags[off] = fault ? uint8_t(0x82) : uint8_t(lv.level());
         }
-        if (fault) atomicAdd(faults, 1ull);
-        acc[0] = (double)drho;
-        acc[1] = (double)jx;
-        acc[2] = (double)jy;
-        acc[3] = (double)dg0 + 0.5 * (double)m2;     // E - C_v rho0
-        acc[4] = (double)s_kl;
-        acc[5] = (double)neq;
-        acc[6] = (double)s_pi;
-        acc[7] = (double)s_q;
+        if (X >= tile_x * TX && Y >= tile_y * TY) {     // not counted by the tile before
+            if (fault) atomicAdd(faults, 1ull);
+            acc[0] = (double)drho;
+            acc[1] = (double)jx;
+            acc[2] = (double)jy;
+            acc[3] = (double)dg0 + 0.5 * (double)m2;     // E - C_v rho0
+            acc[4] = (double)s_kl;
+            acc[5] = (double)neq;
+            acc[6] = (double)s_pi;
+            acc[7] = (double)s_q;
+        }
     }
-    block_sums_n<NT / kWave>(acc, partials + (long long)blockIdx.x * kNsums);
+    block_sums_n<NT / kWave>(acc, partials + (long long)tile * kNsums);
 }
 
 // The g update of the double distribution: g is staged with its halo like
@@ -1204,9 +1214,10 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfGWav
     const int nx = a.nx, ny = a.ny;
     const long long plane = a.plane;
     int tile_x, tile_y;
-    xcd_tile(a, tile_x, tile_y);
+    const int tile = xcd_tile(a, tile_x, tile_y);
+    if (tile < 0) return;                       // whole workgroups
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-    const int X0 = tile_x * TX, Y0 = tile_y * TY;
+    const int X0 = tile_origin<EDGE>(tile_x, TX, nx), Y0 = tile_origin<EDGE>(tile_y, TY, ny);
     const int X = X0 + tx, Y = Y0 + ty;
     const bool active = !EDGE || (X < nx && Y < ny);     // EDGE: as in d2q25_kernel
     const TileStage<S, TX, TY> st(a, X0, Y0, tx, ty);
@@ -1271,6 +1282,12 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfGWav
     });
 }
 
+// The non-temporal population stores where rows are whole 64-byte pieces: a
+// partial line that leaves the cache early is written twice (plain / hint, us
+// per step: double distribution 2001 x 1501 495 / 543, 2024 x 1500 486 / 498, 2000
+// x 1500 467 / 461; single 2001 x 1501 215 / 247).
+constexpr int kNtRow = 16;
+
 template <typename S, int TX, int TY>
 static hipError_t launch_ddf_tile(const D2Q25Args& a, const void* fin, void* fout, void* sens,
                                   uint8_t* flags, double* partials, unsigned long long* faults,
@@ -1283,31 +1300,30 @@ static hipError_t launch_ddf_tile(const D2Q25Args& a, const void* fin, void* fou
     using R = typename Store<S>::real;
     if (a.tile_x != TX || a.tile_y != TY) return hipErrorInvalidValue;
     if (!a.aux) return hipErrorInvalidValue;
-    // the same EDGE form with and without the extension sensors (as above);
-    // the non-temporal stores on whole FP32 tiles whose rows are whole
-    // 128-byte lines only (on the f kernel's 16-float rows they wrote 717
+    // the same EDGE form with and without the extension sensors; the
+    // non-temporal stores on FP32 tiles whose rows are whole 128-byte lines only (on the f kernel's 16-float rows they wrote 717
     // instead of 614 MB per step at 2048^2)
-    const bool whole = a.nx % TX == 0 && a.ny % TY == 0;
+    const bool whole = a.nx >= TX && a.ny >= TY;
     constexpr bool kNT = std::is_same<S, float>::value && TX * sizeof(R) >= 128;
-    const bool nt = kNT && whole && a.nt_stores;
+    const bool nt = kNT && whole && a.nt_stores && a.nx % kNtRow == 0;
     const bool ext = a.x.mask && !a.quiet;
     if (ext && nt)
-        d2q25_ddf_kernel<S, TX, TY, true, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, true, false, kNT><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (ext && whole)
-        d2q25_ddf_kernel<S, TX, TY, true, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, true, false><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (ext)
-        d2q25_ddf_kernel<S, TX, TY, true, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, true, true><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (nt)
-        d2q25_ddf_kernel<S, TX, TY, false, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, false, false, kNT><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (whole)
-        d2q25_ddf_kernel<S, TX, TY, false, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, false, false><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else
-        d2q25_ddf_kernel<S, TX, TY, false, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_ddf_kernel<S, TX, TY, false, true><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     D2Q25Args ag = a;
@@ -1316,14 +1332,14 @@ static hipError_t launch_ddf_tile(const D2Q25Args& a, const void* fin, void* fou
     ag.tiles_x = (a.nx + GX - 1) / GX;
     ag.tiles_y = (a.ny + GY - 1) / GY;
     ag.nblocks = ag.tiles_x * ag.tiles_y;
-    const bool gwhole = a.nx % GX == 0 && a.ny % GY == 0;
+    const bool gwhole = a.nx >= GX && a.ny >= GY;
     constexpr bool kGNT = std::is_same<S, float>::value && GX * sizeof(R) >= 128;
-    if (kGNT && gwhole && a.nt_stores)
-        d2q25_ddf_g_kernel<S, GX, GY, false, kGNT><<<dim3(ag.nblocks), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
+    if (kGNT && gwhole && a.nt_stores && a.nx % kNtRow == 0)
+        d2q25_ddf_g_kernel<S, GX, GY, false, kGNT><<<dim3(xcd_grid(ag)), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
     else if (gwhole)
-        d2q25_ddf_g_kernel<S, GX, GY, false><<<dim3(ag.nblocks), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
+        d2q25_ddf_g_kernel<S, GX, GY, false><<<dim3(xcd_grid(ag)), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
     else
-        d2q25_ddf_g_kernel<S, GX, GY><<<dim3(ag.nblocks), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
+        d2q25_ddf_g_kernel<S, GX, GY><<<dim3(xcd_grid(ag)), dim3(GX * GY), 0, s>>>(ag, (const raw*)fin, (raw*)fout);
     return hipGetLastError();
 }
 
@@ -1335,29 +1351,29 @@ static hipError_t launch_tile(const D2Q25Args& a, const void* fin, void* fout, v
     using R = typename Store<S>::real;
     if (a.tile_x != TX || a.tile_y != TY) return hipErrorInvalidValue;
     // with and without the extension sensors the same EDGE form runs, so the
-    // base outputs stay the same bits; the non-temporal stores on whole FP32
-    // tiles of whole 128-byte rows only
-    const bool whole = a.nx % TX == 0 && a.ny % TY == 0;
+    // base outputs stay the same bits; the non-temporal stores on FP32 tiles
+    // of whole 128-byte rows only
+    const bool whole = a.nx >= TX && a.ny >= TY;
     constexpr bool kNT = std::is_same<S, float>::value && TX * sizeof(R) >= 128;
-    const bool nt = kNT && whole && a.nt_stores;
+    const bool nt = kNT && whole && a.nt_stores && a.nx % kNtRow == 0;
     const bool ext = a.x.mask && !a.quiet;
     if (ext && nt)
-        d2q25_kernel<S, TX, TY, true, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, true, false, kNT><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (ext && whole)
-        d2q25_kernel<S, TX, TY, true, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, true, false><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (ext)
-        d2q25_kernel<S, TX, TY, true, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, true, true><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (nt)
-        d2q25_kernel<S, TX, TY, false, false, kNT><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, false, false, kNT><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else if (whole)
-        d2q25_kernel<S, TX, TY, false, false><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, false, false><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     else
-        d2q25_kernel<S, TX, TY, false, true><<<dim3(a.nblocks), dim3(TX * TY), 0, s>>>(
+        d2q25_kernel<S, TX, TY, false, true><<<dim3(xcd_grid(a)), dim3(TX * TY), 0, s>>>(
             a, (const raw*)fin, (raw*)fout, (R*)sens, flags, partials, faults);
     return hipGetLastError();
 }
