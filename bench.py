@@ -263,8 +263,11 @@ def main():
         return
 
     rho, ux, uy = inputs.smooth_random(n, seed=wl["seed"], cutoff=wl["cutoff"])
+    # --mode kernel profiles the one-step kernel that the roofline entry times
+    # alone; the timed steps leave the number of steps per launch to the library
     lat = lks.Lattice(9, n, n, "f32", tau=wl["tau"], thr=wl["thr"], flag_mask=wl["flag_mask"],
-                      max_steps=max(args.steps, 1), layout=LAYOUT, device=dev)
+                      max_steps=max(args.steps, 1), layout=LAYOUT, device=dev,
+                      launch_steps=1 if args.mode == "kernel" else 0)
     # the initial fields stay on the device: re-initialising the headline
     # state then needs no host transfer (no idle gap before the timed steps)
     fields = [torch.as_tensor(a, dtype=torch.float64).to(dev).contiguous() for a in (rho, ux, uy)]
@@ -340,6 +343,8 @@ def main():
                         "random field (seed 0, 16 modes)",
             "grid": [n, n], "tau": wl["tau"], "lattice": "D2Q9", "layout": LAYOUT,
         },
+        # bytes of one-step launches over the time of a step: several steps per
+        # launch move fewer bytes, and the rate may pass the HBM peak
         "achieved_GBps": round(BYTES_F32_FUSED * n * n / t_step / 1e9, 1),
         "roofline": {
             "bound": "hbm",
@@ -620,7 +625,7 @@ def time_two_step(torch, lks, inputs, workloads, dev, ev, k=32, rounds=RUNS):
         n = wl["nx"]
         rho, ux, uy = inputs.smooth_random(n, seed=wl["seed"], cutoff=wl["cutoff"])
         lats = {}
-        for ls in (0, 2):
+        for ls in (1, 2):
             lat = lks.Lattice(9, n, n, "f32", tau=wl["tau"], thr=wl["thr"] or workloads.SMOOTH_4096["thr"],
                               flag_mask=wl["flag_mask"], max_steps=64, layout=LAYOUT, launch_steps=ls,
                               device=dev)
@@ -628,17 +633,17 @@ def time_two_step(torch, lks, inputs, workloads, dev, ev, k=32, rounds=RUNS):
             lat.step(60)
             lats[ls] = lat
         torch.cuda.synchronize()
-        times = {0: [], 2: []}
+        times = {1: [], 2: []}
         for _ in range(rounds):
             for ls, lat in lats.items():
                 median_time(torch, ev, 1, lambda: lat.step(k), out=times[ls])
         med = {ls: sorted(t)[len(t) // 2] / k for ls, t in times.items()}
         res[f"f32_{n}"] = {"grid": [n, n],
-                           "one_step": {"MLUPS": round(n * n / med[0] / 1e6, 1),
-                                        "us_per_step": round(med[0] * 1e6, 1)},
+                           "one_step": {"MLUPS": round(n * n / med[1] / 1e6, 1),
+                                        "us_per_step": round(med[1] * 1e6, 1)},
                            "two_step": {"MLUPS": round(n * n / med[2] / 1e6, 1),
                                         "us_per_step": round(med[2] * 1e6, 1)},
-                           "speedup": round(med[0] / med[2], 3)}
+                           "speedup": round(med[1] / med[2], 3)}
         del lats, lat
         torch.cuda.empty_cache()
     return res
