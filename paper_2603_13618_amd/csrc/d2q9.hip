@@ -1401,13 +1401,22 @@ hipError_t launch_d2q9_two(int dtype, const D2Q9Args& a, const void* fin, void* 
     }
 }
 
+// Grids that the tile kernel takes: its tiles fit, and the element indexes of
+// the state, which it forms in 32 bits, lie below 2^32 (477 million cells; a
+// grid that long and too narrow for the band kernel, whose indexes have 64
+// bits, runs the row kernel).
+static bool tile_takes(int nx, int ny, int TX, int TY, int K)
+{
+    return tile_fits(nx, TX, K) && tile_fits(ny, TY, K) && 9LL * nx * ny <= 1LL << 32;
+}
+
 template <typename S, int TX, int TY, int K>
 static hipError_t launch_tile_steps(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                                     uint8_t* flags, double* partials, int first, unsigned long long* faults,
                                     hipStream_t st)
 {
     using G = TileSteps<S, TX, TY, K>;
-    if (k < 1 || k > K || !tile_fits(a.nx, TX, K) || !tile_fits(a.ny, TY, K)) return hipErrorInvalidValue;
+    if (k < 1 || k > K || !tile_takes(a.nx, a.ny, TX, TY, K)) return hipErrorInvalidValue;
     const int cells = (TX + 2 * (k - 1)) * (TY + 2 * (k - 1));
     const int threads = cells >= G::kThreads ? G::kThreads : (cells + kWave - 1) / kWave * kWave;
     const unsigned blocks = (unsigned)(((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY));
@@ -1490,16 +1499,16 @@ int d2q9_tile_of(int dtype, int nx, int ny)
 {
     constexpr long long kCUs = 256;
 #define LKS_TILE_FITS(V, TX, TY, K)                                                                         \
-    if ((V < 3 || dtype != 0) && tile_fits(nx, TX, K) && tile_fits(ny, TY, K) &&                            \
+    if ((V < 3 || dtype != 0) && tile_takes(nx, ny, TX, TY, K) &&                                           \
         (long long)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) <= kCUs)                                     \
         return V;
     LKS_TILE_FORMS(LKS_TILE_FITS)
 #undef LKS_TILE_FITS
     if (band_fits(nx, ny, 3) && band_tiles(nx, ny, 3) >= 8 * kCUs) return kTallForm;
     if (band_fits(nx, ny, 2)) return kBandForm;
-    if (dtype != 0 && tile_fits(nx, 32, 5) && tile_fits(ny, 16, 5)) return 3;
-    if (tile_fits(nx, 16, 7) && tile_fits(ny, 16, 7)) return 2;
-    return tile_fits(nx, 8, 7) && tile_fits(ny, 8, 7) ? 1 : 0;
+    if (dtype != 0 && tile_takes(nx, ny, 32, 16, 5)) return 3;
+    if (tile_takes(nx, ny, 16, 16, 7)) return 2;
+    return tile_takes(nx, ny, 8, 8, 7) ? 1 : 0;
 }
 
 int d2q9_tile_steps(int tile)

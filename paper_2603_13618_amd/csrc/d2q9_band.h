@@ -9,7 +9,7 @@ namespace lks {
 
 // Whether the tiles of T cells with a ring of K along an axis of n cells reach
 // at most one period beyond it on either side (what the kernels wrap).
-constexpr bool tile_fits(int n, int T, int K) { return n >= K && (n - 1) / T * T + T + K <= 2 * n; }
+constexpr bool tile_fits(int n, int T, int K) { return n >= K && (n - 1LL) / T * T + T + K <= 2LL * n; }
 
 // K steps of a tile of 64 columns: eight waves (two a SIMD: six and twelve
 // measured 30 % slower) of NR rows each, one lane a column.  Cells of the tile
