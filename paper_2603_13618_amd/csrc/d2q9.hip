@@ -89,10 +89,17 @@ template <typename R> struct CellSense {
 // EXACT (without SENSE): the equilibrium goes to the collision through opaque
 // copies, as its other uses in the sensors would make it, so that the
 // post-collision state is the same bits as with SENSE.
-template <typename R, bool SENSE, bool COLLIDE, bool EXT = false, bool EXACT = false>
+// read: whether anyone reads the cell's sensors.  A lane that owns no cell holds
+// what the lane shifts or the staging area left there, mostly far from any
+// equilibrium, and would send its wave through the far branch of S_KL row after row
+// (us a step of two steps per launch with / without, 4096^2: FP32 245 / 190, BF16
+// 303 / 215, FP64 767 / 408; one step on 1001 x 1503 with extension sensors 54.6 /
+// 50.1).
+template <typename R, bool SENSE, bool COLLIDE, bool EXT = false, bool EXACT = false,
+          typename Read = std::true_type>
 __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau, R& drho_out,
-                                                    R& jx_out, R& jy_out, R* ext = nullptr,
-                                                    unsigned ext_mask = 0)
+                                                    R& jx_out, R& jy_out, Read read = {},
+                                                    R* ext = nullptr, unsigned ext_mask = 0)
 {
     // moments of the deviation form: rho - rho0 = sum d, j = sum c d
     const R drho = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])) + d[8];
@@ -153,6 +160,7 @@ __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau
             // |x| <= 0.1 already implies it.
             // Cells within the longer series (most of them) take that alone.
             far = !(xmax <= KlShortCut<R>::v);
+            if constexpr (!std::is_same<Read, std::true_type>::value) far = far && read;
             if (far) {
                 kl = R(0);
                 const bool series = xmax <= KlCut<R>::v;
@@ -319,7 +327,7 @@ __global__ __launch_bounds__(kBlock) LKS_CELL_KERNEL_ATTR void d2q9_kernel(
                 for (int i = 0; i < 9; ++i) dc[i] = cur[i][k];
                 R drho, jx, jy;
                 LKS_CELL_BARRIER();
-                const CellSense<R> cs = cell_update<R, SENSE, COLLIDE>(dc, rho0, inv_tau, drho, jx, jy);
+                const CellSense<R> cs = cell_update<R, SENSE, COLLIDE>(dc, rho0, inv_tau, drho, jx, jy, active);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) cur[i][k] = dc[i];
                 if constexpr (SENSE) {
@@ -572,8 +580,8 @@ __global__ __launch_bounds__(kBlock) LKS_CELL_KERNEL_ATTR void d2q9_fused_lds(
             R drho, jx, jy;
             R xv[kNumExt];
             LKS_CELL_BARRIER();
-            const CellSense<R> cs = cell_update<R, true, true, EXT>(dc, rho0, inv_tau, drho, jx, jy, xv,
-                                                                    a.x.mask);
+            const CellSense<R> cs = cell_update<R, true, true, EXT>(dc, rho0, inv_tau, drho, jx, jy, active,
+                                                                    xv, a.x.mask);
 #pragma unroll
             for (int i = 0; i < 9; ++i) res[i][k] = dc[i];
             LevelAcc lv;
@@ -1331,7 +1339,7 @@ __global__ __launch_bounds__(kBlock) void d2q9_fused2_kernel(
                 R e[9];
                 gather_pull(e, aprev3, aprev2, aprev);
                 R drho2, jx2, jy2;
-                const CellSense<R> cs2 = cell_update<R, true, true>(e, rho0, inv_tau, drho2, jx2, jy2);
+                const CellSense<R> cs2 = cell_update<R, true, true>(e, rho0, inv_tau, drho2, jx2, jy2, own_col);
                 if (own_col) {
                     store_cell(q - 3, e, cs2);
                     add_sums(acc_b, nfault, drho2, jx2, jy2, cs2);
@@ -1342,8 +1350,8 @@ __global__ __launch_bounds__(kBlock) void d2q9_fused2_kernel(
                 R d[9];
                 gather_pull(d, prev2, prev, cur);
                 R drho, jx, jy;
-                const CellSense<R> cs = cell_update<R, true, true>(d, rho0, inv_tau, drho, jx, jy);
                 const bool own_a = own_col && ya >= Yb && ya < Ye;
+                const CellSense<R> cs = cell_update<R, true, true>(d, rho0, inv_tau, drho, jx, jy, own_a);
                 if (own_a) add_sums(acc_a, nfault, drho, jx, jy, cs);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
