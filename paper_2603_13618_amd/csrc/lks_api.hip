@@ -416,9 +416,6 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
-    // FP64 extension sensors need two cells per thread: the call fails in its
-    // first step
-    if (cfg.ext_mask && cfg.dtype == LKS_F64 && vec == 1) a.tile = c->nblocks_t = c->slots_t = 0;
     c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0,
                                                   cfg.layout == LKS_LAYOUT_ROWS, vec == wide_vec(cfg.dtype));
     c->last_t = c->single_t && !cfg.ext_mask;
@@ -490,6 +487,18 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
     return LKS_OK;
 }
 
+// Whether steps of this context can compute its sensors: the D2Q9 extension
+// sensors in FP64 run with two cells per thread.  Asked before the first launch
+// of a call, so that a refused call leaves state, buffers and step count as
+// they were.
+lks_status ext_runs(lks_ctx* c)
+{
+    if (c->cfg.lattice == LKS_D2Q9 && c->cfg.ext_mask && c->cfg.dtype == LKS_F64 && c->a9.g.vec == 1)
+        return fail(c, LKS_EHIP, "step kernel: FP64 extension sensors need an even nx, 16-byte aligned buffers "
+                    "and launch_vec 0 or 2");
+    return LKS_OK;
+}
+
 // The step loop of lks_step and lks_step_noalloc (c valid).
 lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
 {
@@ -500,6 +509,8 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
     if (q25 && !fused) return fail(c, LKS_EUNSUPPORTED, "the unfused passes exist for D2Q9 only");
     if (c->cfg.ext_mask && !fused)
         return fail(c, LKS_EUNSUPPORTED, "extension sensors are computed by the fused step only");
+    if (nsteps == 0) return LKS_OK;
+    if (lks_status st = ext_runs(c)) return st;
     const lks::D2Q9Args& a = c->a9;
     int done = 0;
     while (done < nsteps) {
@@ -850,6 +861,7 @@ lks_status lks_step_from(lks_ctx* c, const void* src, void* dst)
     if (!c) return LKS_EINVAL;
     if (!src || !dst) return fail(c, LKS_EINVAL, "src and dst are required");
     if (src == dst) return fail(c, LKS_EINVAL, "src and dst must differ");
+    if (lks_status s = ext_runs(c)) return s;
     hipError_t e = c->cfg.lattice == LKS_D2Q25
                        ? lks::launch_d2q25(c->cfg.dtype, c->a25, src, dst, c->buf.sensors,
                                            c->buf.flags, c->partials, c->faults, c->stream)
