@@ -1543,11 +1543,6 @@ int d2q9_tile_blocks(int tile, int nx, int ny)
     }
 }
 
-bool d2q9_tile_single(int dtype, int tile, bool nt, bool rows, bool wide)
-{
-    return (tile != kBandForm && tile != kTallForm) || dtype > 1 || !nt || !rows || !wide;
-}
-
 template <typename S>
 static hipError_t launch_tile_form(const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                                    uint8_t* flags, double* partials, int first, unsigned long long* faults,

@@ -291,8 +291,7 @@ struct lks_ctx {
     int nblocks2;          // workgroups of the two-step launches (launch_steps 2), else 0
     int nblocks_t;         // workgroups of the tile launches (a9.tile), else 0
     int slots_t;           // steps whose tile partial sums fit (1 .. kMaxChunk)
-    bool single_t;         // single steps run in the tile form too
-    bool last_t;           // and a call's last step (it computes the extension sensors)
+    bool last_t;           // a call's last step too (it computes the extension sensors)
     double* partials;
     unsigned long long* faults;
     char err[kErrLen];     // fixed storage: reporting an error allocates nothing
@@ -416,9 +415,7 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
-    c->single_t = a.tile && lks::d2q9_tile_single(cfg.dtype, a.tile, a.nt_stores != 0,
-                                                  cfg.layout == LKS_LAYOUT_ROWS, vec == wide_vec(cfg.dtype));
-    c->last_t = c->single_t && !cfg.ext_mask;
+    c->last_t = a.tile && !cfg.ext_mask;
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -447,13 +444,11 @@ lks_status finalize(lks_ctx* c, int nblocks, int nsteps, int64_t row0)
 // form.  An odd number, so that the state changes buffer as often as with one
 // step per launch, and the call's last step alone: the other buffer then holds
 // the state before it, as with one step per launch.  As even a split over the
-// fewest launches as that allows; where single steps run in the row kernel
-// (band form), threes and at most three single steps at the end.
+// fewest launches as that allows.
 int tile_part(const lks_ctx* c, int left)
 {
     const int most = lks::d2q9_tile_steps(c->a9.tile), m = left - 1;
     if (m == 0) return 1;
-    if (!c->single_t) return m >= most ? most : 1;
     int q = (m + most - 1) / most;
     if ((q ^ m) & 1) ++q;
     const int p = m / q;
@@ -471,7 +466,7 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
         // of the launch's p steps, those among the call's last max_steps
         const int behind = left - m - c->cfg.max_steps;
         const int first = behind <= 0 ? 0 : (behind < p ? behind : p);
-        if ((p == 1 && !(left - m == 1 ? c->last_t : c->single_t)) || kept + p - first > c->slots_t) break;
+        if ((left - m == 1 && !c->last_t) || kept + p - first > c->slots_t) break;
         hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, c->a9, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
                                              c->buf.sensors, c->buf.flags,
                                              c->partials + (size_t)kept * c->nblocks_t * lks::kNsumsHost, first,

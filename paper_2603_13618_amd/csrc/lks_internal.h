@@ -117,17 +117,15 @@ hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin
                             uint8_t* flags, double* partials, int first, unsigned long long* faults,
                             hipStream_t s);
 // The tile form for a grid (0 = none), the most steps a launch of it takes and
-// its workgroups.
+// its workgroups.  All steps of a call run in it, single ones too, so that a
+// step's sums are the same bits wherever a run is split into calls.  That costs
+// calls of one to three steps on FP32 and FP64 row-interleaved states beyond the
+// last-level cache, whose single steps the row kernel (launch_steps = 1) takes
+// faster: a call of one step, row kernel / tile form, FP32 4096^2 248 / 261 us,
+// 8192^2 940 / 1020, FP64 4096^2 477 / 498, 8192^2 1908 / 2050.
 int d2q9_tile_of(int dtype, int nx, int ny);
 int d2q9_tile_steps(int tile);
 int d2q9_tile_blocks(int tile, int nx, int ny);
-// Whether single steps run in the tile form too: not on FP32 and FP64
-// row-interleaved states beyond the last-level cache (nt) whose rows the row
-// kernel takes with its widest accesses.  One step, row kernel / tile form:
-// FP32 4096^2 246 / 253 us, 8192^2 952 / 1019, FP64 4096^2 499 / 508; but BF16
-// 184 / 176, FP32 plane-major 4096^2 287 / 263, odd rows (one cell per thread)
-// FP32 4001 x 3000 260 / 236, FP64 757 / 420.
-bool d2q9_tile_single(int dtype, int tile, bool nt, bool rows, bool wide);
 
 hipError_t launch_d2q25(int dtype, const D2Q25Args& a, const void* fin, void* fout, void* sens,
                         uint8_t* flags, double* partials, unsigned long long* faults,
