@@ -242,6 +242,18 @@ __device__ __forceinline__ CellSense<R> cell_update(R (&d)[9], R rho0, R inv_tau
     return out;
 }
 
+// flag levels of the extension sensors
+template <typename R>
+__device__ __forceinline__ void ext_levels(const D2Q9Args& a, const R (&xv)[kNumExt], LevelAcc& lv)
+{
+    constexpr bool F32 = sizeof(R) == 4;
+#pragma unroll
+    for (int q = 0; q < kNumExt; ++q) {
+        if (!(a.mask & (1u << (kExtFlagShift + q)))) continue;
+        lv.add(xv[q], F32 ? R(a.x.thr_f[q][0]) : R(a.x.thr[q][0]), F32 ? R(a.x.thr_f[q][1]) : R(a.x.thr[q][1]));
+    }
+}
+
 template <typename S, int VEC, bool PULL>
 __device__ __forceinline__ void load_row(const typename Store<S>::raw* __restrict__ fin, const PopLayout& L,
                                          int y, int nx, int ny, int x0, bool active, int lane,
@@ -590,14 +602,8 @@ __global__ __launch_bounds__(kBlock) LKS_CELL_KERNEL_ATTR void d2q9_fused_lds(
             for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
             if constexpr (EXT) {
 #pragma unroll
-                for (int q = 0; q < kNumExt; ++q) {
-                    xres[q][k] = xv[q];
-                    if (a.mask & (1u << (kExtFlagShift + q))) {
-                        const R t0 = F32 ? R(a.x.thr_f[q][0]) : R(a.x.thr[q][0]);
-                        const R t1 = F32 ? R(a.x.thr_f[q][1]) : R(a.x.thr[q][1]);
-                        lv.add(xv[q], t0, t1);
-                    }
-                }
+                for (int q = 0; q < kNumExt; ++q) xres[q][k] = xv[q];
+                ext_levels(a, xv, lv);
             }
             fl[k] = cs.fault ? uint8_t(0x82) : uint8_t(lv.level());
             s_kl[k] = cs.kl;
@@ -635,6 +641,12 @@ __global__ __launch_bounds__(kBlock) LKS_CELL_KERNEL_ATTR void d2q9_fused_lds(
 // FP32, us per step of a 64-step call (the one-step row kernel in brackets):
 // 64^2 1.8 (14.8), 128^2 1.9 (16.4), 256^2 2.6 (16.1); FP64 128^2 3.4 (14.9),
 // BF16 256^2 2.5 (7.1).
+// EXT: a call's last step with the extension sensors (K = 1; no staging buffer).
+// Here and in the band kernel below one cell per lane holds 100-108 registers
+// (FP64 164-192) where the row kernel with four holds 247 (FP64, two: 312), so
+// that two to four times as many waves hide its latency.  A call of one step with
+// nine of them, us, the row kernel in brackets: FP32 128^2 11.2 (14.4), 512^2 16.2
+// (21.5), 2048^2 123 (141-149), 4096^2 445 (486); FP64 512^2 38 (45), 2048^2 517 (560).
 template <typename S, int TX, int TY, int K> struct TileSteps {
     using raw = typename Store<S>::raw;
     using R = typename Store<S>::real;
@@ -665,7 +677,7 @@ __device__ __forceinline__ double wave_sum_lane63(double v)
     return v;
 }
 
-template <typename S, int TX, int TY, int K>
+template <typename S, int TX, int TY, int K, bool EXT = false>
 __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile_kernel(
     D2Q9Args a, int k, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
     typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
@@ -674,7 +686,7 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
     using G = TileSteps<S, TX, TY, K>;
     using R = typename G::R;
     using raw = typename G::raw;
-    __shared__ raw buf[2][9 * G::kCells];
+    __shared__ raw buf[2][K > 1 ? 9 * G::kCells : 1];
     __shared__ R terms[2][G::kSums][G::kTile];
 
     const int nx = a.nx, ny = a.ny;
@@ -725,7 +737,7 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
             const int x = e - r * W - h, y = r - h;
             const int cell = (y + h0) * W0 + x + h0;
             R d[9];
-            if (j == 0) {
+            if (K == 1 || j == 0) {
                 const int gx = X0 + x, gy = Y0 + y;
                 // one period off at most (tile_fits)
                 unsigned xs[3], ys[3];
@@ -749,8 +761,10 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
                     d[i] = Store<S>::to_real(src[i * G::kCells + cell - cy9(i) * W0 - cx9(i)]);
             }
             R drho, jx, jy;
-            const CellSense<R> cs = cell_update<R, true, true>(d, rho0, inv_tau, drho, jx, jy);
-            if (!last) {
+            R xv[EXT ? kNumExt : 1];
+            const CellSense<R> cs = cell_update<R, true, true, EXT>(d, rho0, inv_tau, drho, jx, jy, {}, xv,
+                                                                    a.x.mask);
+            if (K > 1 && !last) {
                 raw* dst = buf[j & 1];
 #pragma unroll
                 for (int i = 0; i < 9; ++i) dst[i * G::kCells + cell] = Store<S>::from_real(d[i]);
@@ -777,6 +791,12 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
                         const R sv[3] = {cs.kl, cs.neq, cs.pi};
 #pragma unroll
                         for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                        if constexpr (EXT) {
+                            ext_levels(a, xv, lv);
+#pragma unroll
+                            for (int q = 0; q < kNumExt; ++q)
+                                if (a.x.plane[q] >= 0) sens[a.x.plane[q] * a.plane + off] = xv[q];
+                        }
                         sens[off] = cs.kl;
                         sens[plane + off] = cs.neq;
                         sens[2 * plane + off] = cs.pi;
@@ -850,13 +870,13 @@ __device__ __forceinline__ double wave_sums6(const double (&v)[6], bool upper8)
     return s + dpp_move<0xb1>(s);                                       // quad_perm 1 0 3 2
 }
 
-template <typename S, int K, int NR, bool NT>
-__global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 ? 4 : 2))) void d2q9_band_kernel(
+template <typename S, int K, int NR, bool NT, bool EXT = false>
+__global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 && !EXT ? 4 : 2))) void d2q9_band_kernel(
     D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,
     typename Store<S>::real* __restrict__ sens, uint8_t* __restrict__ flags, double* __restrict__ partials,
     int first, int nblocks, unsigned long long* __restrict__ faults)
 {
-    static_assert(K == 1 || K == 3, "one or three steps");
+    static_assert(K == 1 || (K == 3 && !EXT), "one or three steps, extension sensors in single ones");
     using G = Band<K, NR>;
     using R = typename Store<S>::real;
     using raw = typename Store<S>::raw;
@@ -903,7 +923,9 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
             const int y = G::NR * wave + r;
             const bool own = X0 + lane < nx && Y0 + y < ny;
             R drho, jx, jy;
-            const CellSense<R> cs = cell_update<R, true, true>(d[r], rho0, inv_tau, drho, jx, jy);
+            R xv[EXT ? kNumExt : 1];
+            const CellSense<R> cs = cell_update<R, true, true, EXT>(d[r], rho0, inv_tau, drho, jx, jy, {}, xv,
+                                                                    a.x.mask);
             t[r][0] = drho;
             t[r][1] = jx;
             t[r][2] = jy;
@@ -926,6 +948,15 @@ __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per
                     const R sv[3] = {cs.kl, cs.neq, cs.pi};
 #pragma unroll
                     for (int s = 0; s < 3; ++s) lv.add(sv[s], th[s][0], th[s][1]);
+                    if constexpr (EXT) {
+                        ext_levels(a, xv, lv);
+#pragma unroll
+                        for (int q = 0; q < kNumExt; ++q) {
+                            const R x[1] = {xv[q]};
+                            if (a.x.plane[q] >= 0)
+                                store_pack<R, 1, NT>(sens + (a.x.plane[q] * a.plane + srow) + X, x);
+                        }
+                    }
                     const R kl[1] = {cs.kl}, neq[1] = {cs.neq}, pi[1] = {cs.pi};
                     const uint8_t fl[1] = {cs.fault ? uint8_t(0x82) : uint8_t(lv.level())};
                     store_pack<R, 1, NT>(sens + srow + X, kl);
@@ -1428,6 +1459,18 @@ static hipError_t launch_tile_steps(const D2Q9Args& a, int k, const void* fin, v
     const int cells = (TX + 2 * (k - 1)) * (TY + 2 * (k - 1));
     const int threads = cells >= G::kThreads ? G::kThreads : (cells + kWave - 1) / kWave * kWave;
     const unsigned blocks = (unsigned)(((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY));
+    if (a.x.mask) {
+        // extension sensors: single steps of F32 and F64 states
+        if constexpr (std::is_same<S, float>::value || std::is_same<S, double>::value) {
+            if (k != 1) return hipErrorInvalidValue;
+            using G1 = TileSteps<S, TX, TY, 1>;
+            d2q9_tile_kernel<S, TX, TY, 1, true><<<dim3(blocks), dim3(G1::kThreads), 0, st>>>(
+                a, 1, (const typename G::raw*)fin, (typename G::raw*)fout, (typename G::R*)sens, flags, partials,
+                first, faults);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     d2q9_tile_kernel<S, TX, TY, K><<<dim3(blocks), dim3(threads), 0, st>>>(
         a, k, (const typename G::raw*)fin, (typename G::raw*)fout, (typename G::R*)sens, flags, partials, first,
         faults);
@@ -1452,6 +1495,18 @@ static hipError_t launch_band_steps(const D2Q9Args& a, int k, const void* fin, v
     const raw* in = (const raw*)fin;
     raw* out = (raw*)fout;
     R* sv = (R*)sens;
+    if (a.x.mask) {
+        // extension sensors: single steps of F32 and F64 states
+        if constexpr (std::is_same<S, float>::value || std::is_same<S, double>::value) {
+            if (k != 1) return hipErrorInvalidValue;
+            if (nt)
+                d2q9_band_kernel<S, 1, NR, true, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+            else
+                d2q9_band_kernel<S, 1, NR, false, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     if (k == 3 && nt)
         d2q9_band_kernel<S, 3, NR, true><<<grid, block, 0, st>>>(a, in, out, sv, flags, partials, first, n, faults);
     else if (k == 3)

@@ -291,7 +291,6 @@ struct lks_ctx {
     int nblocks2;          // workgroups of the two-step launches (launch_steps 2), else 0
     int nblocks_t;         // workgroups of the tile launches (a9.tile), else 0
     int slots_t;           // steps whose tile partial sums fit (1 .. kMaxChunk)
-    bool last_t;           // a call's last step too (it computes the extension sensors)
     double* partials;
     unsigned long long* faults;
     char err[kErrLen];     // fixed storage: reporting an error allocates nothing
@@ -362,16 +361,6 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     // widest vector the row length and buffer alignment allow (or the hint)
     const size_t sb = store_bytes(cfg.dtype);
     int vec = cfg.launch_vec > 0 ? cfg.launch_vec : wide_vec(cfg.dtype);
-    // FP32 extension sensors (247 registers with four cells per thread): one cell
-    // per thread on grids of few workgroups, a quarter of the serial work
-    // (512^2, nine sensors: 35.8 -> 22.1 us a step; 1024^2, 512 workgroups, 45.1
-    // against 47.3), and where rows of four cells per thread leave more threads
-    // idle, which compute all the same (620 x 2000: 61 -> 54 us, 300 x 2000 60 -> 38; 2048^2
-    // 147 against 149)
-    if (cfg.ext_mask && cfg.dtype == LKS_F32 && cfg.launch_vec == 0) {
-        const lks::GridShape g = d2q9_shape(cfg, vec), one = d2q9_shape(cfg, 1);
-        if (g.nblocks < 512 || 5LL * one.tiles_x < 4LL * g.tiles_x * vec) vec = 1;
-    }
     const size_t vbytes = sb * vec;
     if (cfg.nx % vec != 0 || !aligned(buf.pop[0], vbytes) || !aligned(buf.pop[1], vbytes) ||
         !aligned(buf.sensors, sens_bytes(cfg.dtype) * vec) || !aligned(buf.flags, vec))
@@ -415,7 +404,6 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
     if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
-    c->last_t = a.tile && !cfg.ext_mask;
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -455,9 +443,10 @@ int tile_part(const lks_ctx* c, int left)
     return p % 2 ? p : (p + 1 <= most && m - (p + 1) >= q - 1 ? p + 1 : p - 1);
 }
 
-// A batch of tile launches: as many of the call's `left` remaining steps as
-// one reduction launch can take, no single step that belongs to the row kernel.  The sums of steps that a later step of the call overwrites are not
-// kept.  *taken = steps run (0: the next step belongs to the row kernel).
+// A batch of tile launches: as many of the call's `left` >= 1 remaining steps
+// as one reduction launch can take (*taken).  The sums of steps that a later step
+// of the call overwrites are not kept; the extension sensors are computed in
+// the call's last step.
 lks_status tile_batch(lks_ctx* c, int left, int* taken)
 {
     int m = 0, kept = 0;
@@ -466,8 +455,10 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
         // of the launch's p steps, those among the call's last max_steps
         const int behind = left - m - c->cfg.max_steps;
         const int first = behind <= 0 ? 0 : (behind < p ? behind : p);
-        if ((left - m == 1 && !c->last_t) || kept + p - first > c->slots_t) break;
-        hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, c->a9, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
+        if (kept + p - first > c->slots_t) break;
+        lks::D2Q9Args a = c->a9;
+        if (left - m > 1) a.x.mask = 0;
+        hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, a, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
                                              c->buf.sensors, c->buf.flags,
                                              c->partials + (size_t)kept * c->nblocks_t * lks::kNsumsHost, first,
                                              c->faults, c->stream);
@@ -483,9 +474,10 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
 }
 
 // Whether steps of this context can compute its sensors: the D2Q9 extension
-// sensors in FP64 run with two cells per thread.  Asked before the first launch
-// of a call, so that a refused call leaves state, buffers and step count as
-// they were.
+// sensors in FP64 take rows that two cells per thread divide, which their
+// one-step kernel needs (the kernels on tiles would run any).  Asked before
+// the first launch of a call, so that a refused call leaves state, buffers and
+// step count as they were.
 lks_status ext_runs(lks_ctx* c)
 {
     if (c->cfg.lattice == LKS_D2Q9 && c->cfg.ext_mask && c->cfg.dtype == LKS_F64 && c->a9.g.vec == 1)
@@ -509,15 +501,13 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
     const lks::D2Q9Args& a = c->a9;
     int done = 0;
     while (done < nsteps) {
-        int singles = nsteps - done;            // steps for the one-step (or two-step) kernels
         if (fused && !q25 && a.tile) {
             int taken = 0;
             if (lks_status st = tile_batch(c, nsteps - done, &taken)) return st;
             done += taken;
-            if (taken) continue;
-            singles = nsteps - done;            // the last few, in the row kernel
+            continue;
         }
-        int m = singles < c->chunk ? singles : c->chunk;
+        int m = (nsteps - done) < c->chunk ? (nsteps - done) : c->chunk;
         // two steps per launch: the batch takes whole pairs; a step without a
         // partner (the odd end of a call, or batches of one) is a batch of
         // its own in the one-step kernel
@@ -860,7 +850,7 @@ lks_status lks_step_from(lks_ctx* c, const void* src, void* dst)
     hipError_t e = c->cfg.lattice == LKS_D2Q25
                        ? lks::launch_d2q25(c->cfg.dtype, c->a25, src, dst, c->buf.sensors,
                                            c->buf.flags, c->partials, c->faults, c->stream)
-                   : c->last_t
+                   : c->a9.tile
                        ? lks::launch_d2q9_tile(c->cfg.dtype, c->a9, 1, src, dst, c->buf.sensors, c->buf.flags,
                                                c->partials, 0, c->faults, c->stream)
                        : lks::launch_d2q9(c->cfg.dtype, lks::kFused, c->a9, src, dst,

@@ -45,3 +45,20 @@ def _run_and_compare(a, b):
 @pytest.mark.parametrize("layout", ["rows", "planes"])
 def test_any_split_gives_the_same_bits(dtype, nx, ny, layout):
     _run_and_compare(*_pair(nx, ny, dtype, layout))
+
+
+# the tile kernel's forms, the bands with two and three rows a wave, both stores
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("layout", ["rows", "planes"])
+@pytest.mark.parametrize("nx,ny", [(40, 33), (150, 130), (300, 280), (700, 334), (1968, 1971), (4096, 772)])
+def test_any_split_gives_the_same_bits_with_extension_sensors(dtype, nx, ny, layout):
+    thr = np.full((lks.MAX_EXT, 2), np.inf)
+    thr[lks.EXT_NAMES.index("kn")] = (1e-3, 1e-2)
+    kw = dict(ext=("kn", "alpha", "strain"), thr_ext=thr)
+    a, b = _pair(nx, ny, dtype, layout, **kw)
+    _run_and_compare(a, b)
+    row = _pair(nx, ny, dtype, layout, launch_steps=1, **kw)[0]      # the one-step kernel
+    row.step(sum(CALLS))
+    torch.cuda.synchronize()
+    for x, y in ((a.state, row.state), (a.sensors, row.sensors), (a.flags, row.flags)):
+        assert torch.equal(_bits(x), _bits(y))
