@@ -241,7 +241,8 @@ typedef struct {
 
 /* Device bytes of scratch for the configuration (per-block FP64 partial
  * sums and counters; lks_create also takes a smaller buffer that holds the
- * partial sums of the one-step kernels, and then runs those; with
+ * partial sums of the one-step kernels, and then takes fewer steps per launch
+ * or, where one step's sums over tiles do not fit either, runs those kernels; with
  * LKS_MODEL_DDF also 6 values per cell that the step's f kernel hands to its g
  * kernel).  0 for an invalid configuration. */
 size_t lks_scratch_bytes(const lks_config* cfg);

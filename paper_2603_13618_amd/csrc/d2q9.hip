@@ -1586,6 +1586,13 @@ int d2q9_tile_steps(int tile)
     }
 }
 
+int d2q9_tile_steps_upto(int tile, int n)
+{
+    const int most = d2q9_tile_steps(tile);
+    if (n >= most) return most;
+    return tile == kBandForm || tile == kTallForm ? 1 : (n - 1) / 2 * 2 + 1;      // n >= 1
+}
+
 int d2q9_tile_blocks(int tile, int nx, int ny)
 {
     switch (tile) {

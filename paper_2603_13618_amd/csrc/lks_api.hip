@@ -191,12 +191,16 @@ lks::D2Q25Args d2q25_args(const lks_config& c)
 }
 
 // The tile form of a configuration's fused steps (0 = none): automatic launch
-// shapes only.
+// shapes only, and only where one step's partial sums fit the array that
+// lks_step_noalloc has for them, so that its sums are those of lks_step (up to
+// 262,140 tiles: 402 million cells in bands of three rows a wave).
 int tile_of(const lks_config& c)
 {
     if (c.lattice != LKS_D2Q9 || c.launch_steps || c.launch_rows || c.launch_vec || c.launch_nt)
         return 0;
-    return lks::d2q9_tile_of(c.dtype, c.nx, c.ny);
+    const int tile = lks::d2q9_tile_of(c.dtype, c.nx, c.ny);
+    const size_t one = (size_t)lks::d2q9_tile_blocks(tile, c.nx, c.ny) * lks::kNsumsHost * sizeof(double);
+    return one <= (size_t)LKS_NOALLOC_SCRATCH_BYTES - kHeader ? tile : 0;
 }
 
 // workgroups of one step's cell kernel: the most any vector width that
@@ -238,8 +242,9 @@ int tile_kept(const lks_config& c, int tile)
 }
 
 // bytes of partial sums without and with the tile form's workgroups: the
-// first is the least lks_create takes (a scratch buffer of that size runs the
-// row kernels where the tile form's partials do not fit), the second what
+// first is the least lks_create takes (a scratch buffer of that size takes fewer
+// steps a launch, or runs the row kernels where no step's partials over the
+// tiles fit), the second what
 // lks_scratch_bytes asks for (room for the steps of one tile launch at least)
 size_t least_partials(const lks_config& c) { return partials_for(c, step_blocks(c)); }
 size_t partials_bytes(const lks_config& c)
@@ -291,6 +296,7 @@ struct lks_ctx {
     int nblocks2;          // workgroups of the two-step launches (launch_steps 2), else 0
     int nblocks_t;         // workgroups of the tile launches (a9.tile), else 0
     int slots_t;           // steps whose tile partial sums fit (1 .. kMaxChunk)
+    int most_t;            // most steps of a tile launch
     double* partials;
     unsigned long long* faults;
     char err[kErrLen];     // fixed storage: reporting an error allocates nothing
@@ -398,12 +404,16 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     c->a25.nt_stores = a.nt_stores;
     c->nblocks = cfg.lattice == LKS_D2Q25 ? c->a25.nblocks : a.g.nblocks;
     c->nblocks2 = cfg.launch_steps == 2 ? lks::d2q9_two_blocks(cfg.dtype, cfg.nx, cfg.ny) : 0;
-    // the tile form where the partial sums that one launch may keep fit
+    // the tile form where the partial sums of one step fit; where those that a
+    // launch of the form's most steps may keep do not, with fewer steps a launch
+    // (the sums are the same bits)
     a.tile = tile_of(cfg);
     c->nblocks_t = lks::d2q9_tile_blocks(a.tile, cfg.nx, cfg.ny);
     const size_t slots = a.tile ? partials / ((size_t)c->nblocks_t * lks::kNsumsHost * sizeof(double)) : 0;
     c->slots_t = (int)(slots < (size_t)kMaxChunk ? slots : (size_t)kMaxChunk);
-    if (a.tile && c->slots_t < tile_kept(cfg, a.tile)) a.tile = c->nblocks_t = c->slots_t = 0;
+    if (c->slots_t < 1) a.tile = c->nblocks_t = c->slots_t = 0;
+    c->most_t = lks::d2q9_tile_steps(a.tile);
+    if (c->slots_t < tile_kept(cfg, a.tile)) c->most_t = lks::d2q9_tile_steps_upto(a.tile, c->slots_t);
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -435,7 +445,7 @@ lks_status finalize(lks_ctx* c, int nblocks, int nsteps, int64_t row0)
 // fewest launches as that allows.
 int tile_part(const lks_ctx* c, int left)
 {
-    const int most = lks::d2q9_tile_steps(c->a9.tile), m = left - 1;
+    const int most = c->most_t, m = left - 1;
     if (m == 0) return 1;
     int q = (m + most - 1) / most;
     if ((q ^ m) & 1) ++q;

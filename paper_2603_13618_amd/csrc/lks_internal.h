@@ -116,8 +116,8 @@ int d2q9_two_blocks(int dtype, int nx, int ny);
 hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin, void* fout, void* sens,
                             uint8_t* flags, double* partials, int first, unsigned long long* faults,
                             hipStream_t s);
-// The tile form for a grid (0 = none), the most steps a launch of it takes and
-// its workgroups.  All steps of a call run in it, single ones too, so that a
+// The tile form for a grid (0 = none), the most steps a launch of it takes, the
+// most of at most n >= 1, and its workgroups.  All steps of a call run in it, single ones too, so that a
 // step's sums are the same bits wherever a run is split into calls.  That costs
 // calls of one to three steps on FP32 and FP64 row-interleaved states beyond the
 // last-level cache, whose single steps the row kernel (launch_steps = 1) takes
@@ -125,6 +125,7 @@ hipError_t launch_d2q9_tile(int dtype, const D2Q9Args& a, int k, const void* fin
 // 8192^2 940 / 1020, FP64 4096^2 477 / 498, 8192^2 1908 / 2050.
 int d2q9_tile_of(int dtype, int nx, int ny);
 int d2q9_tile_steps(int tile);
+int d2q9_tile_steps_upto(int tile, int n);
 int d2q9_tile_blocks(int tile, int nx, int ny);
 
 hipError_t launch_d2q25(int dtype, const D2Q25Args& a, const void* fin, void* fout, void* sens,
