@@ -1000,7 +1000,17 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
             });
         };
         if (xmax <= KlCut<R>::v) closed([](R x) { return x * x * kl_series(x); });
-        else closed([](R x) { return kl_phi(x); });
+        // FP32: a branch per population, so that the general form runs for those
+        // in which some cell of the wave is beyond the longer series (us a step,
+        // without / with: a weak shock on 1024 x 2 29.6 / 25.0, Riemann quadrants
+        // on 320 x 1024 70.8 / 65.6, on 1024^2 175 / 170); FP64 computes both
+        // forms and selects (1024 x 2 34.2 / 38.7, 500 x 301 81 / 85)
+        else closed([](R x) {
+            if constexpr (sizeof(R) == 8) return kl_phi(x);
+            R phi = x * x * kl_series(x);
+            if (!(fabs(x) <= KlCut<R>::v)) phi = kl_general(x);
+            return phi;
+        });
     }
     // the total energy flux q = sum v (g^neq + |v|^2/2 f^neq) (S_Q), and the
     // heat fluxes relative to u: with sum f^neq = 0 and sum v f^neq = 0,
