@@ -5,8 +5,9 @@ Workload: smooth random field (seed 0, 16 Fourier modes), D2Q9 BGK, 4096x4096
 periodic, tau = 0.52, FP32 deviation storage in the row-interleaved layout
 ([ny][9][nx]; --layout planes for [9][ny][nx]); one step = pull streaming +
 moments + equilibrium + S_KL, S_NEQ, S_PI + refinement flags + BGK collision +
-FP64 global sums, all in one kernel (plus one small reduction kernel per
-batch of steps).  Inputs are resident in HBM before the timed region starts.
+FP64 global sums.  The library runs three steps per launch (sensors and flags of
+a call's last step are stored, the sums of every step) and one small reduction
+kernel per batch of steps.  Inputs are resident in HBM before the timed region starts.
 
     python bench.py [--steps K] [--warmup W] [--gpus 1] [--no-cpu] [--cpu-full] [--forms]
                     [--ext] [--ddf] [--q25] [--regrid] [--no-two-step]
@@ -30,10 +31,16 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, vendor figure
 BYTES_F32_FUSED = 85            # 9 x 4 read + 9 x 4 written + 3 x 4 sensors + 1 flag
+STEPS_PER_LAUNCH = 3            # the library's choice on 64-column bands
 BYTES_F32_PLAIN = 193           # stream 36 + 36, sensors 36 + 13, collide 36 + 36
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_d2q9_fused_f32_4096.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_2603_13618_amd", "csrc", "d2q9.hip")
-# the fused FP32 step at the default launch shape (4 cells per thread)
+# the kernel of the timed steps: three steps of a 64 x 24 tile per launch, a
+# call's last step a launch of its own (<float,1,3,true>); bound by VALU issue
+# (profiles/d2q9_band_f32_4096.md)
+BAND_KERNEL = "d2q9_band_kernel<float,3,3,true>"
+# the fused FP32 step with one step per launch (4 cells per thread), the HBM
+# roofline's kernel
 # (non-temporal stores: the two 604 MB state buffers exceed the last-level cache)
 FUSED_KERNEL = "d2q9_fused_lds<float,4,false,true>"
 FUSED_KERNEL_PREFIX = "d2q9_fused_lds"     # rocprofv3 prints the bare name
@@ -50,6 +57,15 @@ LAYOUT = "rows"                 # population layout of every lattice (--layout)
 
 
 RUNS = 5                        # timed runs per measurement; the median is reported
+
+
+def call_bytes(steps, state, out):
+    """HBM bytes per cell of one call of `steps` D2Q9 steps in launches of
+    STEPS_PER_LAUNCH: each launch reads and writes the state (`state` bytes each
+    way); single steps, the last one among them, write sensors and flags
+    (`out`) too."""
+    several, singles = divmod(steps - 1, STEPS_PER_LAUNCH)
+    return several * 2 * state + (singles + 1) * (2 * state + out)
 
 
 def warm_up(torch, work, seconds=0.04):
@@ -124,8 +140,8 @@ def parse():
                    help="population layout of every lattice: plane-major [Q][ny][nx] or "
                         "row-interleaved [ny][Q][nx]")
     p.add_argument("--mode", choices=["bench", "kernel", "copy"], default="bench")
-    p.add_argument("--workload", choices=["smooth4096", "riemann2048", "smooth8192-bf16",
-                                          "smooth8192-f16", "adjoint1024", "smooth4096-ext",
+    p.add_argument("--workload", choices=["smooth4096", "smooth4096-band", "riemann2048",
+                                          "smooth8192-bf16", "smooth8192-f16", "adjoint1024", "smooth4096-ext",
                                           "riemann2048-ext", "riemann2048-ddf", "riemann2048-ddf-ext",
                                           "smooth4096-two", "smooth8192-two"],
                    default="smooth4096", help="workload of --mode kernel (profiling runs)")
@@ -307,17 +323,23 @@ def main():
     faults = lat.check()
     mlups = n * n / t_step / 1e6
 
-    # ---- the fused kernel alone: back-to-back launches between the two
-    #      state buffers, bracketed by events on the same stream, median of RUNS
+    # ---- the fused kernel with one step per launch alone: back-to-back
+    #      launches between the two state buffers, bracketed by events on the
+    #      same stream, median of RUNS
     reps = max(args.steps, 10)
-    src, dst = lat.pop[lat.current()[0]], lat.pop[1 - lat.current()[0]]
-    lat.step_from(src, dst)
+    one = lks.Lattice(9, n, n, "f32", tau=wl["tau"], thr=wl["thr"], flag_mask=wl["flag_mask"],
+                      layout=LAYOUT, device=dev, launch_steps=1)
+    one.restore(lat.state)
+    src, dst = one.pop
+    one.step_from(src, dst)
     torch.cuda.synchronize()
 
     def alone():
         for r in range(reps):
-            lat.step_from(src, dst) if r % 2 == 0 else lat.step_from(dst, src)
+            one.step_from(src, dst) if r % 2 == 0 else one.step_from(dst, src)
     t_kernel = median_time(torch, ev, RUNS, alone) / reps
+    del one, src, dst
+    step_bytes = call_bytes(args.steps, 36, 13) / args.steps
     achieved = BYTES_F32_FUSED * n * n / t_kernel / 1e9
     traffic = traffic_entry(n * n)
 
@@ -343,9 +365,16 @@ def main():
                         "random field (seed 0, 16 modes)",
             "grid": [n, n], "tau": wl["tau"], "lattice": "D2Q9", "layout": LAYOUT,
         },
-        # bytes of one-step launches over the time of a step: several steps per
-        # launch move fewer bytes, and the rate may pass the HBM peak
-        "achieved_GBps": round(BYTES_F32_FUSED * n * n / t_step / 1e9, 1),
+        # the bytes that the timed launches move, per step, over the time of a step
+        "achieved_GBps": round(step_bytes * n * n / t_step / 1e9, 1),
+        "launch": {
+            "kernel": BAND_KERNEL,
+            "steps_per_launch": STEPS_PER_LAUNCH,
+            "bound": "valu",
+            "bytes_per_lup": round(step_bytes, 2),
+            "frac_hbm": round(step_bytes * n * n / t_step / 1e9 / HBM_PEAK_GBPS, 4),
+        },
+        # one step per launch, timed alone
         "roofline": {
             "bound": "hbm",
             "achieved": round(achieved, 1),
@@ -354,6 +383,7 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": traffic,
             "kernel": FUSED_KERNEL,
+            "steps_per_launch": 1,
             "bytes_per_launch": BYTES_F32_FUSED * n * n,
             "kernel_us": round(t_kernel * 1e6, 2),
             "copy_GBps": round(copy_gbps, 1),
@@ -480,7 +510,8 @@ def ext_lattices(lks, inputs, workloads, dev, steps):
 
 def time_ext(torch, lks, inputs, workloads, dev, ev):
     """Fused steps with every extension sensor on (timing only): D2Q9, the
-    single and the double distribution on D2Q25."""
+    single and the double distribution on D2Q25.  One step per call, since a
+    call computes these sensors in its last step."""
     k = 40
     a, b = ext_lattices(lks, inputs, workloads, dev, k)
     c = ddf_lattice(lks, inputs, workloads, dev, k, ext=EXTDDF)
@@ -488,8 +519,11 @@ def time_ext(torch, lks, inputs, workloads, dev, ev):
     for name, lat, nbytes in (("d2q9_4096_f32_ext9", a, 85 + 4 * len(EXT9)),
                               ("d2q25_2048_f32_ext8", b, 217 + 4 * len(EXT25)),
                               ("d2q25_ddf_2048_f32_ext10", c, BYTES_F32_DDF + 4 * len(EXTDDF))):
+        def steps():
+            for _ in range(k):
+                lat.step(1)
         warm_up(torch, lambda: lat.step(1))
-        t = median_time(torch, ev, RUNS, lambda: lat.step(k)) / k
+        t = median_time(torch, ev, RUNS, steps) / k
         cells = lat.nx * lat.ny
         res[name] = {"MLUPS": round(cells / t / 1e6, 1), "us_per_step": round(t * 1e6, 1),
                      "GBps_model": round(nbytes * cells / t / 1e9, 1), "bytes_per_lup": nbytes,
@@ -566,11 +600,15 @@ def time_d2q25(torch, ev, lat, k, name, kernel, bpl):
 
 def kernel_only(args, torch, lks, inputs, workloads, dev):
     """A short run of one of the other workloads (for profilers)."""
-    if args.workload == "riemann2048-ddf-ext":
-        ddf_lattice(lks, inputs, workloads, dev, args.steps, ext=EXTDDF).step(args.steps)
-    elif args.workload.endswith("-ext"):
-        a, b = ext_lattices(lks, inputs, workloads, dev, args.steps)
-        (a if args.workload.startswith("smooth") else b).step(args.steps)
+    if args.workload.endswith("-ext"):
+        # one step per call: a call computes the extension sensors in its last step
+        if args.workload == "riemann2048-ddf-ext":
+            lat = ddf_lattice(lks, inputs, workloads, dev, args.steps, ext=EXTDDF)
+        else:
+            a, b = ext_lattices(lks, inputs, workloads, dev, args.steps)
+            lat = a if args.workload.startswith("smooth") else b
+        for _ in range(args.steps):
+            lat.step(1)
     elif args.workload == "riemann2048-ddf":
         ddf_lattice(lks, inputs, workloads, dev, args.steps).step(args.steps)
     elif args.workload == "riemann2048":
@@ -582,6 +620,14 @@ def kernel_only(args, torch, lks, inputs, workloads, dev):
                           bc=(1, 1), thr=wl["thr"], flag_mask=wl["flag_mask"],
                           max_steps=max(args.steps, 1), layout=LAYOUT, device=dev)
         lat.init(rho, ux, uy, T)
+        lat.step(args.steps)
+    elif args.workload == "smooth4096-band":
+        wl = workloads.SMOOTH_4096
+        n = wl["nx"]
+        rho, ux, uy = inputs.smooth_random(n, seed=wl["seed"], cutoff=wl["cutoff"])
+        lat = lks.Lattice(9, n, n, "f32", tau=wl["tau"], thr=wl["thr"], flag_mask=wl["flag_mask"],
+                          max_steps=max(args.steps, 1), layout=LAYOUT, device=dev)
+        lat.init(rho, ux, uy)
         lat.step(args.steps)
     elif args.workload.endswith("-two"):
         wl = workloads.SMOOTH_4096 if args.workload.startswith("smooth4096") else workloads.SMOOTH_8192
@@ -597,7 +643,8 @@ def kernel_only(args, torch, lks, inputs, workloads, dev):
         n = wl["nx"]
         rho, ux, uy = inputs.smooth_random(n, seed=wl["seed"], cutoff=wl["cutoff"])
         lat = lks.Lattice(9, n, n, args.workload.split("-")[1], tau=wl["tau"], thr=wl["thr"],
-                          flag_mask=wl["flag_mask"], max_steps=max(args.steps, 1), layout=LAYOUT, device=dev)
+                          flag_mask=wl["flag_mask"], max_steps=max(args.steps, 1), layout=LAYOUT,
+                          launch_steps=1, device=dev)
         lat.init(rho, ux, uy)
         lat.step(args.steps)
     else:
@@ -770,15 +817,16 @@ def time_forms(torch, lks, inputs, workloads, dev, ev):
     n = wl["nx"]
     rho, ux, uy = inputs.smooth_random(n, seed=wl["seed"], cutoff=wl["cutoff"])
     res = {}
-    for dtype, nbytes in (("bf16", 49), ("f16", 49), ("f32", 85)):
+    k = 40
+    for dtype, state in (("bf16", 18), ("f16", 18), ("f32", 36)):
+        nbytes = call_bytes(k, state, 13) / k
         lat = lks.Lattice(9, n, n, dtype, tau=wl["tau"], thr=wl["thr"] or workloads.SMOOTH_4096["thr"],
                           flag_mask=wl["flag_mask"], max_steps=64, layout=LAYOUT, device=dev)
         lat.init(rho, ux, uy)
         warm_up(torch, lambda: lat.step(1))
-        k = 40
         t = median_time(torch, ev, RUNS, lambda: lat.step(k)) / k
         res[dtype] = {"MLUPS": round(n * n / t / 1e6, 1), "GBps_model": round(nbytes * n * n / t / 1e9, 1),
-                      "bytes_per_lup": nbytes, "grid": [n, n]}
+                      "bytes_per_lup": round(nbytes, 2), "steps_per_launch": STEPS_PER_LAUNCH, "grid": [n, n]}
         del lat
         torch.cuda.empty_cache()
     return res

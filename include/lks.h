@@ -223,8 +223,15 @@ typedef struct {
                              fault count are the same bits and the per-step
                              FP64 sums agree to FP64 rounding (each cell's
                              terms are widened to FP64 before any add); with
+                             0 and 1 a step's sums are the same bits however
+                             a run is split into calls; with
                              2 the state changes buffer once per launch, so
-                             lks_current names the buffer that holds it      */
+                             lks_current names the buffer that holds it.
+                             0 is the fastest in calls of four steps and
+                             more; in calls of one to three steps on F32 and
+                             F64 ROWS states beyond the last-level cache 1 is
+                             (F32 4096^2, us a step: 20 steps 135 / 240 / 189
+                             with 0 / 1 / 2, one step 261 with 0, 248 with 1)    */
 } lks_config;
 
 typedef struct {

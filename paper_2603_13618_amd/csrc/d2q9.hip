@@ -812,27 +812,6 @@ __global__ __launch_bounds__((TileSteps<S, TX, TY, K>::kThreads)) void d2q9_tile
     if (nfault) atomicAdd(faults, (unsigned long long)nfault);
 }
 
-// Three steps of one tile per launch, mid-size and large grids.  A one-step
-// kernel moves 85 B per cell and step (FP32) and waits for HBM; three steps
-// for one pass leave the VALU issue as the bound.  A workgroup of eight waves
-// owns 64 columns and 8 NR rows, NR rows a wave, one lane a column.  Step 0 reads
-// its populations from global memory (the tile and a ring of two cells, whose
-// cells are dealt out densely over the waves) and writes the post-collision
-// values, rounded to the storage type, to LDS; step 1 (the tile and a ring of
-// one cell) reads them, holds its results in registers across a barrier and
-// writes them in their place; step 2 stores the state.  In place, the 68 x 20
-// (NR = 2) or 68 x 28 cells take 49 or 69 KB in FP32, so that two workgroups
-// share a CU and one's loads and stores hide behind the other's arithmetic.
-// K = 1: a single step on the same tiles, so that every step's sums are added
-// in the same order whichever launch it runs in.  Cell arithmetic:
-// cell_update (246 VALU instructions, of which ring cells need 100).  A row's
-// sums cost 88 instructions with a reduction of each of the six values; what
-// is left after sharing it (wave_sums6), keeping lanes outside the grid out of
-// it only where there are any, and counting faults by ballot took 142 to 129 us
-// per step at FP32 4096^2, NR = 2.
-// us per step (the one-step row kernel in brackets): FP32 512^2 4.0 (17.5),
-// 1024^2 10.9 (17.9), 2048^2 34 (68.8), 4096^2 122 (239); FP64 1024^2 24
-// (33.6), 4096^2 310 (468); BF16 1024^2 10.9 (16.1), 4096^2 125 (178).
 // Sums over the wave of six values: halves, then 16-lane rows, then 8-lane
 // halves of rows, of two values are exchanged and added (each lane then
 // carries one of them), and the eight lanes that are left added up.  Lanes 0, 16, 32, 48
@@ -870,6 +849,28 @@ __device__ __forceinline__ double wave_sums6(const double (&v)[6], bool upper8)
     return s + dpp_move<0xb1>(s);                                       // quad_perm 1 0 3 2
 }
 
+// Three steps of one tile per launch, mid-size and large grids.  A one-step
+// kernel moves 85 B per cell and step (FP32) and waits for HBM; three steps
+// for one pass leave the VALU issue as the bound.  A workgroup of eight waves
+// owns 64 columns and 8 NR rows, NR rows a wave, one lane a column.  Step 0 reads
+// its populations from global memory (the tile and a ring of two cells, whose
+// cells are dealt out densely over the waves) and writes the post-collision
+// values, rounded to the storage type, to LDS; step 1 (the tile and a ring of
+// one cell) reads them, holds its results in registers across a barrier and
+// writes them in their place; step 2 stores the state.  In place, the 68 x 20
+// (NR = 2) or 68 x 28 cells take 49 or 69 KB in FP32, so that two workgroups
+// share a CU and one's loads and stores hide behind the other's arithmetic.
+// Populations reach their neighbours in x and y through the LDS buffer alone.
+// K = 1: a single step on the same tiles, so that every step's sums are added
+// in the same order whichever launch it runs in.  Cell arithmetic:
+// cell_update (246 VALU instructions, of which ring cells need 100).  A row's
+// sums cost 88 instructions with a reduction of each of the six values; what
+// is left after sharing it (wave_sums6), keeping lanes outside the grid out of
+// it only where there are any, and counting faults by ballot took 142 to 129 us
+// per step at FP32 4096^2, NR = 2.
+// us per step (the one-step row kernel in brackets): FP32 512^2 4.0 (17.5),
+// 1024^2 10.9 (17.9), 2048^2 34 (68.8), 4096^2 122 (239); FP64 1024^2 24
+// (33.6), 4096^2 310 (468); BF16 1024^2 10.9 (16.1), 4096^2 125 (178).
 template <typename S, int K, int NR, bool NT, bool EXT = false>
 __global__ __launch_bounds__(kBandWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(typename Store<S>::real) == 4 && !EXT ? 4 : 2))) void d2q9_band_kernel(
     D2Q9Args a, const typename Store<S>::raw* __restrict__ fin, typename Store<S>::raw* __restrict__ fout,

@@ -196,9 +196,10 @@ __device__ __forceinline__ void store_pack(T* __restrict__ p, const T (&in)[VEC]
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 // FP64: the hardware estimate, two Newton steps and a last residual step, as
 // the compiler's division does without its range scaling (7 instructions
-// instead of 11): 1/x correctly rounded for normal x and 1/x.  Zero, infinite
-// and subnormal x give NaN or infinity; they only occur in cells that are
-// positivity faults whatever the value.
+// instead of 11), for normal x and 1/x.  Zero, infinite and subnormal x give NaN
+// or infinity: equilibrium populations and densities that are zero make the
+// cell a positivity fault whatever the value, and vl_half, whose sum a + b is
+// zero in uniform cells, selects its result only where a b > 0.
 __device__ __forceinline__ double rcp(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
@@ -208,8 +209,8 @@ __device__ __forceinline__ double rcp(double x)
 }
 
 // Quotients by one divisor: its reciprocal once, then each quotient with a
-// residual correction, which rounds it correctly (quotients in the normal
-// range) in three instructions instead of a division's ten.
+// residual correction (quotients in the normal range), three instructions
+// instead of a division's ten.
 template <typename R> struct Divisor {
     R x, r;
     __device__ __forceinline__ explicit Divisor(R v) : x(v), r(rcp(v)) { r = fma(fma(-x, r, R(1)), r, r); }
