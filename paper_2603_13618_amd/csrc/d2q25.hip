@@ -1002,13 +1002,18 @@ __global__ __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(DdfWave
         if (xmax <= KlCut<R>::v) closed([](R x) { return x * x * kl_series(x); });
         // FP32: a branch per population, so that the general form runs for those
         // in which some cell of the wave is beyond the longer series (us a step,
-        // without / with: a weak shock on 1024 x 2 29.6 / 25.0, Riemann quadrants
-        // on 320 x 1024 70.8 / 65.6, on 1024^2 175 / 170); FP64 computes both
-        // forms and selects (1024 x 2 34.2 / 38.7, 500 x 301 81 / 85)
+        // without / with: a weak shock on 1024 x 2 29.7 / 24.8, Riemann quadrants
+        // on 320 x 1024 70.6 / 65.2, on 1024^2 175 / 169; taken by lane instead of by
+        // wave, 1 % slower on the Sod tube, where most populations are beyond);
+        // FP64 computes both forms and selects (1024 x 2 34.2, with branches 38.7)
         else closed([](R x) {
             if constexpr (sizeof(R) == 8) return kl_phi(x);
+            const bool beyond = !(fabs(x) <= KlCut<R>::v);
             R phi = x * x * kl_series(x);
-            if (!(fabs(x) <= KlCut<R>::v)) phi = kl_general(x);
+            if (__builtin_amdgcn_ballot_w64(beyond)) {      // one value for the wave
+                const R g = kl_general(x);
+                phi = beyond ? g : phi;
+            }
             return phi;
         });
     }

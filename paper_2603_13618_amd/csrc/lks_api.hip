@@ -291,6 +291,7 @@ struct lks_ctx {
     bool ready;
     int chunk;
     lks::D2Q9Args a9;
+    lks::D2Q9Args a9_quiet;    // the same without extension sensors
     lks::D2Q25Args a25;
     int nblocks;
     int nblocks2;          // workgroups of the two-step launches (launch_steps 2), else 0
@@ -414,6 +415,8 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     if (c->slots_t < 1) a.tile = c->nblocks_t = c->slots_t = 0;
     c->most_t = lks::d2q9_tile_steps(a.tile);
     if (c->slots_t < tile_kept(cfg, a.tile)) c->most_t = lks::d2q9_tile_steps_upto(a.tile, c->slots_t);
+    c->a9_quiet = a;
+    c->a9_quiet.x.mask = 0;
     // as many steps per reduction launch as the partials area holds for the
     // launch with the most workgroups
     const int nbmax = c->nblocks2 > c->nblocks ? c->nblocks2 : c->nblocks;
@@ -466,10 +469,9 @@ lks_status tile_batch(lks_ctx* c, int left, int* taken)
         const int behind = left - m - c->cfg.max_steps;
         const int first = behind <= 0 ? 0 : (behind < p ? behind : p);
         if (kept + p - first > c->slots_t) break;
-        lks::D2Q9Args a = c->a9;
-        if (left - m > 1) a.x.mask = 0;
-        hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, a, p, c->buf.pop[c->cur], c->buf.pop[1 - c->cur],
-                                             c->buf.sensors, c->buf.flags,
+        const bool quiet = c->cfg.ext_mask && left - m > 1;
+        hipError_t e = lks::launch_d2q9_tile(c->cfg.dtype, quiet ? c->a9_quiet : c->a9, p, c->buf.pop[c->cur],
+                                             c->buf.pop[1 - c->cur], c->buf.sensors, c->buf.flags,
                                              c->partials + (size_t)kept * c->nblocks_t * lks::kNsumsHost, first,
                                              c->faults, c->stream);
         if (lks_status st = hip_check(c, e, "step kernel")) return st;
@@ -546,9 +548,7 @@ lks_status step_impl(lks_ctx* c, int32_t nsteps, int32_t fused)
                                       c->faults, c->stream);
                 if (e == hipSuccess) c->cur = 1 - c->cur;
             } else if (fused) {
-                lks::D2Q9Args q = a;
-                if (!last) q.x.mask = 0;        // the kernel without the extension sensors
-                e = lks::launch_d2q9(c->cfg.dtype, lks::kFused, q, f, g, c->buf.sensors,
+                e = lks::launch_d2q9(c->cfg.dtype, lks::kFused, last ? a : c->a9_quiet, f, g, c->buf.sensors,
                                      c->buf.flags, part, c->faults, c->stream);
                 if (e == hipSuccess) c->cur = 1 - c->cur;
             } else {
