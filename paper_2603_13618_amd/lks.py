@@ -217,7 +217,8 @@ class Lattice:
     launch_steps: fused D2Q9 steps per launch, 0 (default) picks several where
     a call has them, 1 one; 2 runs two (no extension
     sensors; pairs need max_steps >= 2); state, sensors, flags and fault
-    counts are the same bits (the per-step sums agree to FP64 rounding), and
+    counts are the same bits (the per-step sums agree to FP64 rounding; with 0
+    and 1 they are the same bits however a run is split into calls), and
     `state` follows the buffer that holds the current state.
     """
 
