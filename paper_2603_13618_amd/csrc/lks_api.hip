@@ -368,6 +368,17 @@ void setup_ctx(lks_ctx* c, const lks_config& cfg, const lks_buffers& buf, hipStr
     // widest vector the row length and buffer alignment allow (or the hint)
     const size_t sb = store_bytes(cfg.dtype);
     int vec = cfg.launch_vec > 0 ? cfg.launch_vec : wide_vec(cfg.dtype);
+    // FP32 extension sensors in the row kernel (strips of fewer than eight rows,
+    // launch hints): 247 registers with four cells per thread, so one cell
+    // per thread on grids of few workgroups, a quarter of the serial work
+    // (512^2, nine sensors: 35.8 -> 22.1 us a step; 1024^2, 512 workgroups, 45.1
+    // against 47.3), and where rows of four cells per thread leave more threads
+    // idle, which compute all the same (620 x 2000: 61 -> 54 us, 300 x 2000 60 -> 38; 2048^2
+    // 147 against 149)
+    if (cfg.ext_mask && cfg.dtype == LKS_F32 && cfg.launch_vec == 0) {
+        const lks::GridShape g = d2q9_shape(cfg, vec), one = d2q9_shape(cfg, 1);
+        if (g.nblocks < 512 || 5LL * one.tiles_x < 4LL * g.tiles_x * vec) vec = 1;
+    }
     const size_t vbytes = sb * vec;
     if (cfg.nx % vec != 0 || !aligned(buf.pop[0], vbytes) || !aligned(buf.pop[1], vbytes) ||
         !aligned(buf.sensors, sens_bytes(cfg.dtype) * vec) || !aligned(buf.flags, vec))
